@@ -27,9 +27,10 @@
  *    fit a scratch budget of CHIMERA_SCRATCH_MB MiB (environment, read at
  *    each call; default 131072, at least 16), allocated on the index's
  *    device on first need (at most 9/8 of what the batch needs) and kept with
- *    the index.  At 8.8M documents a query needs about 72 MB (its S^T table
- *    and F' row), so the default takes about 1,900 queries per sub-batch, and
- *    a 4096-query batch runs in 3 sub-batches of 1,366 (about 110 GB).  If
+ *    the index.  At 8.8M documents a query needs about 36 MB (its F' row), or
+ *    72 MB where the batch is too small to be scored by document (then its
+ *    S^T table as well), so the default takes about 3,500 queries per
+ *    sub-batch, and a 4096-query batch runs in 2 sub-batches of 2,048.  If
  *    the device cannot hold the arena (other allocations on it), the
  *    sub-batches are halved until it fits; CHIMERA_E_NOMEM only when the
  *    scratch of a single query does not fit.  A sub-batch also holds at

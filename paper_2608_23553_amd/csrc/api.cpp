@@ -122,6 +122,12 @@ static int upload(const HostIndex &h, int device, chimera_index **out) {
     secs.push_back({(void **)&idx->d_rq_g1, h.rq_g1.data(), h.rq_g1.size() * 4, (size_t)kTokenPad * 4 + 256});
     secs.push_back({(void **)&idx->d_rq_signs, h.rq_signs.data(), h.rq_signs.size(), 256});
   }
+  std::vector<uint16_t> cent16;
+  if (f16_tokens_exact(h.cent.data(), (int64_t)h.cent.size(), h.weights.data(), (int)h.weights.size())) {
+    cent16.resize(h.cent.size());
+    f16_of_bf16_grid(h.cent.data(), (int64_t)h.cent.size(), cent16.data());
+    secs.push_back({(void **)&idx->d_cent16, cent16.data(), cent16.size() * 2, 256});
+  }
   size_t need = 0;
   for (auto &s : secs) need += s.bytes;
   size_t free_b = 0, total_b = 0;
@@ -221,14 +227,15 @@ struct Carve {
 
 // Exact bytes the sub-batch loop below carves for nb queries.
 static size_t carve_bytes(const chimera_index *idx, int64_t nb, int TQP, int nprobe, int ncand, Stop stop,
-                          bool rq) {
+                          bool rq, bool by_doc) {
   const int64_t rows = nb * TQP;
   const ProbePlan plan = plan_probe(rows, idx->ncent, nprobe);
   size_t b = 0;
   b += align_up((size_t)rows * 128 * 2);                       // Qs
   b += align_up(probe_part_bytes(plan, rows));                 // partial lists
   b += 2 * align_up((size_t)rows * nprobe * 4);                // cent ids / keys
-  if (stop >= STOP_FULL && !rq) b += align_up((size_t)nb * (idx->ncent + 1) * TQP * 4);  // S^T + sentinel rows
+  if (stop >= STOP_FULL && !rq && !by_doc) b += align_up((size_t)nb * (idx->ncent + 1) * TQP * 4);  // S^T + sentinel rows
+  if (by_doc) b += align_up(doc_score_scratch_bytes(nb, TQP, idx->ndocs, ncand));  // visits by document
   if (rq) b += align_up((size_t)rows * RQ_ROW_BYTES) + align_up((size_t)rows * 4);  // query limbs, qsum
   if (stop >= STOP_CANDIDATES) {
     b += align_up((size_t)nb * idx->ndocs * 4);  // F'
@@ -326,27 +333,41 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
   // sub-batch size: the largest that fits the scratch budget (carve_bytes
   // grows with nb, but not in proportion: the select's chunking depends on nb)
   const size_t budget = own ? scratch_budget() : fixed.bytes;
-  int64_t lo = 1, hi = std::min<int64_t>(nq, 65535);
-  while (lo < hi) {
-    const int64_t mid = lo + (hi - lo + 1) / 2;
-    if (carve_bytes(idx, mid, TQP, nprobe, ncand, stop, o.rabitq) <= budget) lo = mid;
-    else hi = mid - 1;
+  auto largest_for = [&](bool docs) {
+    int64_t lo = 1, hi = std::min<int64_t>(nq, 65535);
+    while (lo < hi) {
+      const int64_t mid = lo + (hi - lo + 1) / 2;
+      if (carve_bytes(idx, mid, TQP, nprobe, ncand, stop, o.rabitq, docs) <= budget) lo = mid;
+      else hi = mid - 1;
+    }
+    // a launch counts its work-items in 32 bits; the scorer runs about 8 per
+    // (query, candidate) (its grid rounds queries up to 8 and candidates up to
+    // 32), so a sub-batch keeps nb * ncand at most 2^28
+    lo = std::min<int64_t>(lo, std::max<int64_t>(1, ((int64_t)1 << 28) / std::max(1, ncand)));
+    // equal sub-batches: the same number of passes, without a short last one
+    const int64_t npass = (nq + lo - 1) / lo;
+    return (nq + npass - 1) / npass;
+  };
+  // scoring by document where a sub-batch's candidates overlap enough
+  // (k_score_docs.hip), by query otherwise
+  bool by_doc = stop == STOP_FULL && !o.rabitq && idx->d_cent16;
+  int64_t B = largest_for(by_doc);
+  if (by_doc && !doc_score_grouped(B, idx->ndocs, idx->ntok, idx->ndense, ncand)) {
+    by_doc = false;
+    B = largest_for(false);
   }
-  int64_t B = lo;
-  // a launch counts its work-items in 32 bits; the scorer runs about 8 per
-  // (query, candidate) (its grid rounds queries up to 8 and candidates up to
-  // 32), so a sub-batch keeps nb * ncand at most 2^28
-  B = std::min<int64_t>(B, std::max<int64_t>(1, ((int64_t)1 << 28) / std::max(1, ncand)));
-  // equal sub-batches: the same number of passes, without a short last one
-  const int64_t npass = (nq + B - 1) / B;
-  B = (nq + npass - 1) / npass;
   auto need_for = [&](int64_t b) {
-    size_t n = carve_bytes(idx, b, TQP, nprobe, ncand, stop, o.rabitq);
-    if (nq % b) n = std::max(n, carve_bytes(idx, nq % b, TQP, nprobe, ncand, stop, o.rabitq));
+    size_t n = carve_bytes(idx, b, TQP, nprobe, ncand, stop, o.rabitq, by_doc);
+    if (nq % b) n = std::max(n, carve_bytes(idx, nq % b, TQP, nprobe, ncand, stop, o.rabitq, by_doc));
     return n;
   };
   size_t need = need_for(B);
   if (!own) {
+    // one query has to fit as it is scored by itself, whatever the batch
+    if (by_doc) {
+      const size_t one = carve_bytes(idx, 1, TQP, nprobe, ncand, stop, o.rabitq, false);
+      if (one > fixed.bytes) need = std::max(need, one), B = 1;
+    }
     while (need > fixed.bytes && B > 1) need = need_for(--B);
     if (need > fixed.bytes)
       return fail(CHIMERA_E_UNSUPPORTED, "one query of this search needs %zu bytes of scratch, more than the "
@@ -391,7 +412,7 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
     uint64_t *part = cv.take<uint64_t>(probe_part_bytes(plan, rows) / 8);
     int32_t *ci = cv.take<int32_t>((size_t)rows * nprobe);
     int32_t *ck = cv.take<int32_t>((size_t)rows * nprobe);
-    float *ST = stop >= STOP_FULL && !o.rabitq ? cv.take<float>((size_t)nb * (idx->ncent + 1) * TQP) : nullptr;
+    float *ST = stop >= STOP_FULL && !o.rabitq && !by_doc ? cv.take<float>((size_t)nb * (idx->ncent + 1) * TQP) : nullptr;
     if (cv.off > scratch_cap) return fail(CHIMERA_E_NOMEM, "internal: scratch plan overflow");
     const size_t qbytes = (size_t)Tq * 128 * (q_dtype == CHIMERA_F32 ? 4 : 2);
     const void *Qb = (const char *)Q + (size_t)q0 * qbytes;
@@ -472,6 +493,11 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
     if (o.rabitq) {
       launch_rq_score(rq.Qi8, rq.qsum, nb, TQP, idx->d_doc_off, idx->d_rq_bits, idx->d_rq_g1, cand, nval,
                       ncand, 0, ncand, fhat, s);
+    } else if (by_doc) {
+      char *w = cv.take<char>(doc_score_scratch_bytes(nb, TQP, idx->ndocs, ncand));
+      if (cv.off > scratch_cap) return fail(CHIMERA_E_NOMEM, "internal: scratch plan overflow");
+      launch_doc_score(Qs, nb, Tq, TQP, idx->d_cent16, idx->d_doc_off, idx->d_cid, idx->d_codes, idx->nbits,
+                       idx->h_weights, idx->ndocs, cand, nval, ncand, w, fhat, s);
     } else {
       launch_residual_score(Qs, nb, Tq, TQP, ST, idx->ncent, idx->d_doc_off, idx->d_cid, idx->d_codes, idx->nbits,
                             idx->h_weights, cand, nval, ncand, 0, ncand, fhat, s);
@@ -523,7 +549,7 @@ void chimera_index_free(chimera_index *idx) {
   void *ptrs[] = {idx->d_cent,    idx->d_doc_off,    idx->d_cid,       idx->d_codes,     idx->d_ivf_off,
                   idx->d_ivf_doc, idx->d_dense_slot, idx->d_doc_dense, idx->d_tok_off,   idx->d_ivf_tok,
                   idx->d_tok_doc, idx->scratch,      idx->d_check,     idx->d_deleted,   idx->d_rq_bits,
-                  idx->d_rq_g1,   idx->d_rq_signs};
+                  idx->d_rq_g1,   idx->d_rq_signs,   idx->d_cent16};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   collab_free(idx);
@@ -655,12 +681,12 @@ int chimera_index_compact(chimera_index *idx) {
                      (void **)&idx->d_codes,     (void **)&idx->d_ivf_off,    (void **)&idx->d_ivf_doc,
                      (void **)&idx->d_dense_slot, (void **)&idx->d_doc_dense, (void **)&idx->d_tok_off,
                      (void **)&idx->d_ivf_tok,   (void **)&idx->d_tok_doc,    (void **)&idx->d_rq_bits,
-                     (void **)&idx->d_rq_g1,     (void **)&idx->d_rq_signs};
+                     (void **)&idx->d_rq_g1,     (void **)&idx->d_rq_signs,   (void **)&idx->d_cent16};
     void **theirs[] = {(void **)&fresh->d_cent,      (void **)&fresh->d_doc_off,    (void **)&fresh->d_cid,
                        (void **)&fresh->d_codes,     (void **)&fresh->d_ivf_off,    (void **)&fresh->d_ivf_doc,
                        (void **)&fresh->d_dense_slot, (void **)&fresh->d_doc_dense, (void **)&fresh->d_tok_off,
                        (void **)&fresh->d_ivf_tok,   (void **)&fresh->d_tok_doc,    (void **)&fresh->d_rq_bits,
-                       (void **)&fresh->d_rq_g1,     (void **)&fresh->d_rq_signs};
+                       (void **)&fresh->d_rq_g1,     (void **)&fresh->d_rq_signs,   (void **)&fresh->d_cent16};
     for (size_t i = 0; i < sizeof(mine) / sizeof(mine[0]); ++i) {
       if (*mine[i]) (void)hipFree(*mine[i]);
       *mine[i] = *theirs[i];

@@ -158,6 +158,23 @@ void launch_residual_score(const uint16_t *Qs, int64_t nq, int Tq, int TQP, cons
                            const uint16_t *weights_host, const int32_t *cand_ids, const int32_t *n_valid,
                            int ncand, int lo, int hi, int32_t *fhat, hipStream_t s);
 
+// Residual scoring of a batch by document (k_score_docs.hip): the same fhat
+// of every kept candidate, without S^T, for an index whose decoded tokens are
+// exact in fp16.  f16_tokens_exact: whether they are (n centroid components
+// and the bucket weights, all bf16); f16_of_bf16_grid: grid values of at most
+// 1 in magnitude as fp16 (cent16 is [ncent][128]).  doc_score_grouped: whether
+// the candidates of nq queries overlap enough for it on an index of ntok tokens
+// and ndense dense lists.  scratch holds
+// doc_score_scratch_bytes bytes (no initial contents needed).
+bool f16_tokens_exact(const uint16_t *cent, int64_t n, const uint16_t *weights, int nweights);
+void f16_of_bf16_grid(const uint16_t *src, int64_t n, uint16_t *dst);
+bool doc_score_grouped(int64_t nq, int64_t ndocs, int64_t ntok, int ndense, int ncand);
+size_t doc_score_scratch_bytes(int64_t nq, int TQP, int64_t ndocs, int ncand);
+void launch_doc_score(const uint16_t *Qs, int64_t nq, int Tq, int TQP, const uint16_t *cent16,
+                      const int64_t *doc_off, const int32_t *cid, const uint8_t *codes, int nbits,
+                      const uint16_t *weights_host, int64_t ndocs, const int32_t *cand_ids, const int32_t *n_valid,
+                      int ncand, void *scratch, int32_t *fhat, hipStream_t s);
+
 // RaBitQ document scoring (k_rabitq.hip).  Query preparation: for each of
 // the rows rounded query rows Qs [rows][128], X = 2048 H diag(signs) q as
 // three int8 limbs Qi8 [rows][RQ_ROW_BYTES] (a, b, c with X = a 2^14 + b 2^7
@@ -215,6 +232,7 @@ struct chimera_index {
   int64_t ndocs = 0, ntok = 0, nnz = 0;
   int64_t device_bytes = 0;
   uint16_t *d_cent = nullptr;
+  uint16_t *d_cent16 = nullptr;  // centroids as fp16 [ncent][dim], or null (see f16_tokens_exact)
   int64_t *d_doc_off = nullptr;
   int32_t *d_cid = nullptr;
   uint8_t *d_codes = nullptr;
