@@ -489,9 +489,12 @@ size_t doc_score_scratch_bytes(int64_t nq, int TQP, int64_t ndocs, int ncand) {
 // take most visits and S^T is far larger than an L2, 1.8 and 1.3 (256 queries
 // 7.97 against 8.22 ms and 17.1 against 18.4 ms); at 250,000 documents of 320
 // tokens 0.7 (8 queries 4.5 against 5.2 ms, 32 queries 11.3 against 19.6 ms).
+// Documents of one tile have little to share: at 1,000 documents of 32 tokens
+// and 256 visits each 0.167 against 0.157 ms (41 tokens, 5,000 documents, 80
+// visits each: 0.428 against 0.435 ms), so the line is at 36 tokens.
 bool doc_score_grouped(int64_t nq, int64_t ndocs, int64_t ntok, int ndense, int ncand) {
   const double nv = (double)nq * ncand, per_doc = ndense > 0 ? 2 : 7;
-  return nv >= (1 << 16) && nv * (double)ntok >= per_doc * 64 * (double)ndocs * (double)ndocs;
+  return nv >= (1 << 16) && ntok >= 36 * ndocs && nv * (double)ntok >= per_doc * 64 * (double)ndocs * (double)ndocs;
 }
 
 void launch_doc_score(const uint16_t *Qs, int64_t nq, int Tq, int TQP, const uint16_t *cent16,
@@ -518,7 +521,7 @@ void launch_doc_score(const uint16_t *Qs, int64_t nq, int Tq, int TQP, const uin
   // documents per workgroup: 64, fewer while that leaves under about 6144
   // workgroups
   int ndb = 64;
-  while (ndb > 8 && (ndocs + ndb - 1) / ndb < 6144) ndb >>= 1;
+  while (ndb > 1 && (ndocs + ndb - 1) / ndb < 6144) ndb >>= 1;
   const dim3 grid((unsigned)((ndocs + ndb - 1) / ndb));
 #define CHIMERA_DS(NB, NC)                                                                                           \
   hipLaunchKernelGGL((k_doc_score<NB, NC>), grid, dim3(256), 0, s, Qf, Tq, ncand, cent16, doc_off, cid, codes, w_lo, \
