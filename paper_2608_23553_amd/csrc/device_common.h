@@ -56,6 +56,69 @@ __device__ __forceinline__ int64_t lower_bound_i32(const int32_t *__restrict__ a
   return lo;
 }
 
+// Inclusive prefix sum over the 64 lanes of a wave, by DPP adds.
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
+  int v = (int)x;
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2, 3
+  return (uint32_t)v;
+}
+
+// Exclusive prefix sum of x over a block of W waves and the total.  wsum [W]
+// is shared and free for the next call once every thread has passed a barrier
+// after this one.
+template <int W>
+__device__ __forceinline__ uint32_t block_scan(uint32_t x, uint32_t *wsum, uint32_t &total) {
+  const uint32_t incl = wave_incl_scan(x);
+  if (lane_id() == 63) wsum[threadIdx.x >> 6] = incl;
+  __syncthreads();
+  uint32_t base = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    const uint32_t y = wsum[w];
+    base += w < (int)(threadIdx.x >> 6) ? y : 0;
+    all += y;
+  }
+  total = all;
+  return base + incl - x;
+}
+
+// Radix-select step over the 64 W PER bins of `bins` (16-byte aligned), from the
+// highest bin down, by a block of W waves: the bin where the running count
+// reaches rem (0 < rem <= total) and the count above it; without such a bin
+// (total < rem) found.x stays as it was.  Returns the total.  found and wsum
+// are shared; both are free for the next call after a barrier.
+template <int W, int PER>
+__device__ __forceinline__ uint32_t find_bin(const uint32_t *bins, uint32_t rem, uint32_t *wsum, uint2 *found) {
+  static_assert(PER % 4 == 0, "whole 16-byte groups");
+  const int top = 64 * W * PER - PER * ((int)threadIdx.x + 1);  // this thread's bins: top + PER - 1 down to top
+  uint32_t x[PER], sum = 0;
+#pragma unroll
+  for (int i = 0; i < PER; i += 4) {
+    const uint4 y = *(const uint4 *)(bins + top + i);
+    x[i] = y.x;
+    x[i + 1] = y.y;
+    x[i + 2] = y.z;
+    x[i + 3] = y.w;
+    sum += y.x + y.y + y.z + y.w;
+  }
+  uint32_t total;
+  uint32_t cum = block_scan<W>(sum, wsum, total);
+  if (cum < rem && cum + sum >= rem) {
+#pragma unroll
+    for (int i = PER - 1; i >= 0; --i) {
+      if (cum < rem && cum + x[i] >= rem) *found = make_uint2((uint32_t)(top + i), cum);
+      cum += x[i];
+    }
+  }
+  __syncthreads();
+  return total;
+}
+
 template <class T>
 __device__ __forceinline__ T shfl_xor(T v, int m) {
   return __shfl_xor(v, m, 64);

@@ -1100,6 +1100,187 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_sel_scan(int P, int ncand, Se
   }
 }
 
+// ---------------------------------------------------------------------
+// The select of a small batch: the same result in three launches instead of
+// seven, for chunks of SEL_CHUNK documents where nq chunks of a query are no
+// more than the split select would make (launch_select).  Its time is
+// launches and the latency of each launch's chain, not bytes.
+//  k_keep_list  per chunk: the bin of bits 31..20 from the walk's histogram
+//               (every workgroup finds it for itself), and the chunk's
+//               documents whose top 12 bits reach it, in document order, at a
+//               place of the query's list reserved by one atomic;
+//  k_keep_cut   per query: T and the ties to keep from the list (bits 19..8,
+//               then 7..0), each chunk's kept and tied counts, their prefix
+//               sums, the number of candidates and the padding;
+//  k_sel_write  per chunk, as in the split select.
+// A list that is full (counted past cap) is not used: k_keep_cut and
+// k_sel_write then read the query's F'.
+// One query of 100,000 documents: 54 us in seven launches before, now 22 us;
+// of 2.2M documents 116 us, now 45 us; 16 queries of 1,000 documents 60 us,
+// now 17 us (the list in registers and the prefix sums by DPP are half of
+// that: 35, 61 and 31 us without them).
+constexpr int SEL_CHUNK = 4096;
+constexpr int SEL_MAX_CHUNKS = 3072;  // of a query: their counts are in LDS, 57 KB with the bins
+
+__host__ __device__ inline int64_t keep_cap(int64_t ndocs, int ncand) {
+  return std::min<int64_t>(ndocs, 4 * (int64_t)ncand + 4096);
+}
+
+__global__ __launch_bounds__(SPLIT_THREADS) void k_keep_list(const int32_t *__restrict__ fp,
+                                                             const uint32_t *__restrict__ hist1, int64_t ndocs, int P,
+                                                             int ncand, int64_t cap, int2 *__restrict__ list,
+                                                             uint32_t *__restrict__ nlist, uint2 *__restrict__ part) {
+  constexpr int W = SPLIT_THREADS / 64;
+  __shared__ uint32_t wsum[2][W];
+  __shared__ uint2 s_bin;
+  __shared__ uint32_t s_at;
+  const int64_t q = blockIdx.x / P;
+  const int c = blockIdx.x % P;
+  const int64_t v0 = (int64_t)c * SEL_CHUNK + threadIdx.x * 16, v1 = min(ndocs, (int64_t)(c + 1) * SEL_CHUNK);
+  const int32_t *f = fp + q * ndocs;
+  int32_t x[16];
+  if (((uintptr_t)f & 15) == 0 && v0 + 16 <= v1) {
+#pragma unroll
+    for (int i = 0; i < 16; i += 4) {
+      const int4 y = *(const int4 *)(f + v0 + i);
+      x[i] = y.x;
+      x[i + 1] = y.y;
+      x[i + 2] = y.z;
+      x[i + 3] = y.w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = v0 + i < v1 ? f[v0 + i] : NO_HIT;
+  }
+  const uint32_t nhit = find_bin<W, SEL_BINS / SPLIT_THREADS>(hist1 + q * SEL_BINS, (uint32_t)ncand, wsum[0], &s_bin);
+  const uint32_t b1 = nhit <= (uint32_t)ncand ? 0 : s_bin.x;  // no more hits than candidates: all are listed
+  uint32_t n = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) n += x[i] != NO_HIT && (fp_key(x[i]) >> 20) >= b1;
+  uint32_t tot;
+  uint32_t pos = block_scan<W>(n, wsum[1], tot);
+  if (threadIdx.x == 0) {
+    s_at = tot ? atomicAdd(&nlist[q], tot) : 0;
+    part[q * P + c] = make_uint2(s_at, tot);
+  }
+  __syncthreads();
+  pos += s_at;
+  int2 *L = list + q * cap;
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    if (x[i] != NO_HIT && (fp_key(x[i]) >> 20) >= b1) {
+      if (pos < (uint64_t)cap) L[pos] = make_int2((int)(v0 + i), x[i]);
+      ++pos;
+    }
+}
+
+// Entries of the list a thread keeps in registers over the passes.
+constexpr int KEEP_REGS = 24;
+
+__global__ __launch_bounds__(SEL_THREADS) void k_keep_cut(const int32_t *__restrict__ fp,
+                                                          const uint32_t *__restrict__ hist1, int64_t ndocs, int P,
+                                                          int ncand, int64_t cap, const int2 *__restrict__ list,
+                                                          const uint32_t *__restrict__ nlist,
+                                                          SelState *__restrict__ st, long long *__restrict__ counts,
+                                                          int32_t *__restrict__ out_ids, int32_t *__restrict__ out_keys,
+                                                          int32_t *__restrict__ n_valid) {
+  constexpr int W = SEL_THREADS / 64, PER = SEL_BINS / SEL_THREADS;
+  __shared__ __align__(16) uint32_t hist[2][SEL_BINS];
+  __shared__ uint32_t wsum[5][W];
+  __shared__ uint2 s_bin[3];
+  extern __shared__ uint32_t chunk_n[];  // [P] kept, [P] tied
+  const int64_t q = blockIdx.x;
+  const int64_t nl = nlist[q];
+  const bool from_list = nl <= cap;  // uniform
+  const int64_t n = from_list ? nl : ndocs;
+  const bool in_regs = from_list && n <= KEEP_REGS * SEL_THREADS;  // uniform
+  const int2 *L = list + q * cap;
+  const int32_t *f = fp + q * ndocs;
+  int2 r[KEEP_REGS];
+  if (in_regs) {
+#pragma unroll
+    for (int u = 0; u < KEEP_REGS; ++u) {
+      const int64_t i = threadIdx.x + u * SEL_THREADS;
+      r[u] = i < n ? L[i] : make_int2(0, NO_HIT);
+    }
+  }
+  // g(document, key) of every entry: of the list, or of every hit
+  auto each = [&](auto &&g) {
+    if (in_regs) {
+#pragma unroll
+      for (int u = 0; u < KEEP_REGS; ++u)
+        if (r[u].y != NO_HIT) g(r[u].x, fp_key(r[u].y));
+      return;
+    }
+    for (int64_t i0 = threadIdx.x; i0 < n; i0 += 4 * SEL_THREADS) {
+      int2 e[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t i = i0 + u * SEL_THREADS;
+        e[u] = make_int2(0, NO_HIT);
+        if (i < n) e[u] = from_list ? L[i] : make_int2((int)i, f[i]);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (e[u].y != NO_HIT) g(e[u].x, fp_key(e[u].y));
+    }
+  };
+  for (int i = threadIdx.x; i < 2 * P; i += SEL_THREADS) chunk_n[i] = 0;
+  for (int i = threadIdx.x; i < 2 * SEL_BINS; i += SEL_THREADS) hist[0][i] = 0;
+  const uint32_t nhit = find_bin<W, PER>(hist1 + q * SEL_BINS, (uint32_t)ncand, wsum[0], &s_bin[0]);
+  uint32_t T = 0, need = 0;
+  if (nhit > (uint32_t)ncand) {  // uniform
+    const uint32_t b1 = s_bin[0].x, rem1 = (uint32_t)ncand - s_bin[0].y;
+    each([&](int, uint32_t u) {
+      if ((u >> 20) == b1) atomicAdd(&hist[0][(u >> 8) & 4095u], 1u);
+    });
+    __syncthreads();
+    find_bin<W, PER>(hist[0], rem1, wsum[1], &s_bin[1]);
+    const uint32_t p2 = (b1 << 12) | s_bin[1].x, rem2 = rem1 - s_bin[1].y;
+    each([&](int, uint32_t u) {
+      if ((u >> 8) == p2) atomicAdd(&hist[1][u & 255u], 1u);
+    });
+    __syncthreads();
+    find_bin<W, PER>(hist[1], rem2, wsum[2], &s_bin[2]);
+    T = (p2 << 8) | s_bin[2].x;
+    need = rem2 - s_bin[2].y;
+  }
+  each([&](int d, uint32_t u) {
+    if (u > T) atomicAdd(&chunk_n[d / SEL_CHUNK], 1u);
+    else if (u == T) atomicAdd(&chunk_n[P + d / SEL_CHUNK], 1u);
+  });
+  __syncthreads();
+  // ties before each chunk, then output offsets
+  const int per = (P + SEL_THREADS - 1) / SEL_THREADS;
+  const int c0 = min(P, (int)threadIdx.x * per), c1 = min(P, c0 + per);
+  uint32_t my = 0, all;
+  for (int c = c0; c < c1; ++c) my += chunk_n[P + c];
+  uint32_t tb = block_scan<W>(my, wsum[3], all);
+  my = 0;
+  for (int c = c0; c < c1; ++c) {
+    const uint32_t t = chunk_n[P + c], take = chunk_n[c] + (tb < need ? min(t, need - tb) : 0);
+    counts[3 * (q * P + c) + 1] = tb;
+    counts[3 * (q * P + c) + 2] = take;
+    chunk_n[c] = take;
+    tb += t;
+    my += take;
+  }
+  uint32_t off = block_scan<W>(my, wsum[4], all);
+  for (int c = c0; c < c1; ++c) {
+    counts[3 * (q * P + c)] = off;
+    off += chunk_n[c];
+  }
+  const uint32_t kept = min(all, (uint32_t)ncand);
+  if (threadIdx.x == 0) {
+    st[q] = SelState{0, 0, T, (long long)need, (long long)kept};
+    n_valid[q] = (int32_t)kept;
+  }
+  for (uint32_t i = kept + threadIdx.x; i < (uint32_t)ncand; i += SEL_THREADS) {
+    out_ids[q * ncand + i] = -1;
+    out_keys[q * ncand + i] = 0;
+  }
+}
+
 // Per chunk: the ordered compaction of its kept documents, from the chunk's
 // list when the last pass kept one, else from F'.
 __global__ __launch_bounds__(SPLIT_THREADS) void k_sel_write(const int32_t *__restrict__ fp, int64_t ndocs, int P,
@@ -1107,6 +1288,8 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_sel_write(const int32_t *__re
                                                              const long long *__restrict__ counts, int cap,
                                                              const int2 *__restrict__ clist,
                                                              const uint32_t *__restrict__ clen,
+                                                             const uint32_t *__restrict__ nlist, int64_t qcap,
+                                                             const uint2 *__restrict__ part,
                                                              int32_t *__restrict__ out_ids,
                                                              int32_t *__restrict__ out_keys) {
   __shared__ long long wsum[SPLIT_THREADS / 64];
@@ -1118,10 +1301,13 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_sel_write(const int32_t *__re
   const long long *cc = counts + 3 * (q * P + c);
   if (cc[2] == 0 || cc[0] >= ncand) return;  // uniform: the chunk keeps nothing that fits
   long long written = cc[0], ties_seen = cc[1];
-  const uint32_t nl = clen[q * P + c];
+  // the chunk's list: its own (the split select), or its part of the query's
+  const uint2 pt = part ? part[q * P + c] : make_uint2(0, 0);
+  const uint32_t nl = !part ? clen[q * P + c] : nlist[q] <= qcap ? pt.y : SEL_NO_LIST;
   const bool from_list = nl != SEL_NO_LIST;  // uniform
-  const int2 *L = clist + (q * P + c) * (int64_t)cap;
-  const int64_t per = sel_chunk_docs(ndocs, P), vb = min(ndocs, c * per), ve = min(ndocs, vb + per);
+  const int2 *L = part ? clist + q * qcap + pt.x : clist + (q * P + c) * (int64_t)cap;
+  const int64_t per = part ? SEL_CHUNK : sel_chunk_docs(ndocs, P);
+  const int64_t vb = min(ndocs, c * per), ve = min(ndocs, vb + per);
   const int64_t b0 = from_list ? 0 : vb, b1 = from_list ? (int64_t)nl : ve;
   const int32_t *f = fp + q * ndocs;
   const int64_t step = (int64_t)SPLIT_THREADS * SEL_ITEMS;
@@ -1179,20 +1365,47 @@ int select_chunks(int64_t nq, int64_t ndocs) {
   return (int)std::max<int64_t>(1, std::min(by_q, by_docs));
 }
 
+// Enough queries to fill the chip with one workgroup each, over short enough
+// F' rows: k_select, one launch (measured faster than the split passes at
+// 100,000 documents, slower at 1M; at 256 queries of 100,000 documents 115 us
+// against 150 us for the small batch's three launches).
+static bool select_by_query(int64_t nq, int64_t ndocs) { return nq >= 128 && ndocs < (1 << 19); }
+
+// Chunks of the small batch's select, 0 where it is not used: as long as a
+// chunk of SEL_CHUNK documents is no smaller than the split select's.
+static int keep_chunks(int64_t nq, int64_t ndocs) {
+  if (select_by_query(nq, ndocs)) return 0;
+  const int64_t P = (ndocs + SEL_CHUNK - 1) / SEL_CHUNK;
+  return P <= SEL_MAX_CHUNKS && nq * P <= 16384 ? (int)P : 0;
+}
+
 size_t select_scratch_bytes(int64_t nq, int64_t ndocs, int ncand) {
+  if (const int64_t K = keep_chunks(nq, ndocs))
+    return (size_t)nq * (sizeof(SelState) + (size_t)K * (24 + 8) + (size_t)keep_cap(ndocs, ncand) * 8) + 1024;
   const int P = select_chunks(nq, ndocs);
   const size_t cap = (size_t)sel_list_cap(ndocs, P, ncand);
   return (size_t)nq * (sizeof(SelState) + (SEL_BINS + 256) * 4 + (size_t)P * (24 + 256 * 4 + 4 + 4 + cap * 8)) +
          (size_t)nq * P * (4 + cap * 8) + 1024;
 }
 
-void launch_select(const int32_t *fp, const uint32_t *hist, int64_t nq, int64_t ndocs, int ncand, void *scratch,
-                   int32_t *cand_ids, int32_t *cand_keys, int32_t *n_valid, hipStream_t s) {
+void launch_select(const int32_t *fp, const uint32_t *hist, uint32_t *nlist, int64_t nq, int64_t ndocs, int ncand,
+                   void *scratch, int32_t *cand_ids, int32_t *cand_keys, int32_t *n_valid, hipStream_t s) {
   if (nq <= 0) return;
-  if (nq >= 128 && ndocs < (1 << 19)) {
-    // enough queries to fill the chip with one workgroup each, over short
-    // enough F' rows (one launch; measured faster than the split passes at
-    // 100k documents, slower at 1M)
+  if (const int K = keep_chunks(nq, ndocs)) {
+    const int64_t cap = keep_cap(ndocs, ncand);
+    SelState *st = (SelState *)scratch;
+    long long *counts = (long long *)(st + nq);
+    uint2 *part = (uint2 *)(counts + 3 * nq * K);
+    int2 *list = (int2 *)(part + nq * K);
+    const dim3 gc((unsigned)(nq * K)), tb(SPLIT_THREADS);
+    hipLaunchKernelGGL(k_keep_list, gc, tb, 0, s, fp, hist, ndocs, K, ncand, cap, list, nlist, part);
+    hipLaunchKernelGGL(k_keep_cut, dim3((unsigned)nq), dim3(SEL_THREADS), (size_t)K * 8, s, fp, hist, ndocs, K, ncand,
+                       cap, list, nlist, st, counts, cand_ids, cand_keys, n_valid);
+    hipLaunchKernelGGL(k_sel_write, gc, tb, 0, s, fp, ndocs, K, ncand, st, counts, 0, list, (const uint32_t *)nullptr,
+                       nlist, cap, part, cand_ids, cand_keys);
+    return;
+  }
+  if (select_by_query(nq, ndocs)) {
     hipLaunchKernelGGL((k_select<0>), dim3((unsigned)nq), dim3(SEL_THREADS), 0, s, fp, hist, ndocs, ncand,
                        (const int64_t *)nullptr, cand_ids, cand_keys, n_valid);
     return;
@@ -1218,8 +1431,8 @@ void launch_select(const int32_t *fp, const uint32_t *hist, int64_t nq, int64_t 
   hipLaunchKernelGGL((k_sel_next<8, true>), gq, tb, 0, s, hist3, st);
   hipLaunchKernelGGL(k_sel_scan, gq, tb, 0, s, P, ncand, st, chunk_hist, chunk_above, counts, cand_ids, cand_keys,
                      n_valid);
-  hipLaunchKernelGGL(k_sel_write, gc, tb, 0, s, fp, ndocs, P, ncand, st, counts, cap, clist, clen, cand_ids,
-                     cand_keys);
+  hipLaunchKernelGGL(k_sel_write, gc, tb, 0, s, fp, ndocs, P, ncand, st, counts, cap, clist, clen,
+                     (const uint32_t *)nullptr, (int64_t)0, (const uint2 *)nullptr, cand_ids, cand_keys);
 }
 
 __global__ __launch_bounds__(256) void k_count_hits(const int32_t *__restrict__ fp, int64_t ndocs,

@@ -356,80 +356,106 @@ void launch_residual_score(const uint16_t *Qs, int64_t nq, int Tq, int TQP, cons
 // ---------------------------------------------------------------- top-k
 // One workgroup per query: radix selection of the k-th largest 64-bit key
 // (F^ desc, doc asc) among the kept candidates, then a bitonic sort of the
-// k winners in LDS.
+// k winners in LDS.  The keys' common high bits are skipped (the scores of a
+// query's candidates share most of them) and each pass takes 12 bits, so one
+// or two passes decide; up to TOPK_REGS keys of a thread stay in registers.
+// One query with 16,384 candidates and k = 100: 28.4 us with 8-bit passes from
+// the top over memory, now 18.3 us.
 constexpr int TOPK_THREADS = 1024;
+constexpr int TOPK_REGS = 16;
+constexpr int TOPK_BINS = 4096;
 
 __global__ __launch_bounds__(TOPK_THREADS) void k_topk(const int32_t *__restrict__ fhat,
                                                        const int32_t *__restrict__ cand_ids,
                                                        const int32_t *__restrict__ n_valid, int ncand, int k, int kpow2,
                                                        int32_t *__restrict__ ids, float *__restrict__ scores) {
+  constexpr int W = TOPK_THREADS / 64;
   extern __shared__ uint64_t sk[];  // [kpow2]
-  __shared__ int hist[256];
-  __shared__ unsigned long long s_prefix, s_pmask;
-  __shared__ int s_remaining, s_count, s_done;
+  __shared__ __align__(16) uint32_t hist[TOPK_BINS];
+  __shared__ uint32_t wsum[W];
+  __shared__ uint2 s_bin;
+  __shared__ unsigned long long s_and[W], s_or[W];
+  __shared__ int s_count;
   const int64_t q = blockIdx.x;
   const int n = n_valid[q];
   const int m = min(k, n);
   const int32_t *fh = fhat + q * ncand;
   const int32_t *ci = cand_ids + q * ncand;
+  const bool in_regs = n <= TOPK_REGS * TOPK_THREADS;  // uniform
+  unsigned long long r[TOPK_REGS];  // 0: no key (a real key is larger)
+  if (in_regs) {
+#pragma unroll
+    for (int u = 0; u < TOPK_REGS; ++u) {
+      const int i = threadIdx.x + u * TOPK_THREADS;
+      r[u] = i < n ? pack_key(fh[i], (uint32_t)ci[i]) : 0;
+    }
+  }
+  auto each = [&](auto &&g) {
+    if (in_regs) {
+#pragma unroll
+      for (int u = 0; u < TOPK_REGS; ++u)
+        if (r[u]) g(r[u]);
+    } else {
+      for (int i = threadIdx.x; i < n; i += TOPK_THREADS) g(pack_key(fh[i], (uint32_t)ci[i]));
+    }
+  };
 
   unsigned long long T = 0;  // every key >= T is taken
   if (n > k) {
-    if (threadIdx.x == 0) { s_prefix = 0; s_pmask = 0; s_remaining = k; s_done = 0; }
-    for (int pass = 0; pass < 8; ++pass) {
-      const int shift = 56 - 8 * pass;
-      for (int b = threadIdx.x; b < 256; b += TOPK_THREADS) hist[b] = 0;
-      __syncthreads();
-      const unsigned long long prefix = s_prefix, pmask = s_pmask;
-      for (int i = threadIdx.x; i < n; i += TOPK_THREADS) {
-        const unsigned long long K = pack_key(fh[i], (uint32_t)ci[i]);
-        if ((K & pmask) == prefix) atomicAdd(&hist[(K >> shift) & 255], 1);
-      }
-      __syncthreads();
-      if (threadIdx.x < 64) {
-        // wave 0 finds the bin holding the rem-th largest key: lane l covers
-        // bins 255 - 4l .. 252 - 4l, counts above it come from a lane scan
-        const int lane = threadIdx.x, rem = s_remaining;
-        int local = 0;
+    unsigned long long a = ~0ull, o = 0;
+    each([&](unsigned long long K) {
+      a &= K;
+      o |= K;
+    });
 #pragma unroll
-        for (int i = 0; i < 4; ++i) local += hist[255 - 4 * lane - i];
-        int incl = local;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-          const int y = __shfl_up(incl, d, 64);
-          if (lane >= d) incl += y;
-        }
-        int cum = incl - local;
-        if (cum < rem && incl >= rem) {
-          for (int i = 0; i < 4; ++i) {
-            const int b = 255 - 4 * lane - i;
-            if (cum + hist[b] >= rem) {
-              s_remaining = rem - cum;
-              s_prefix = prefix | ((unsigned long long)b << shift);
-              s_pmask = pmask | (255ull << shift);
-              // the whole bin is needed: every key >= the bin's base is taken
-              s_done = hist[b] == rem - cum;
-              break;
-            }
-            cum += hist[b];
-          }
-        }
-      }
-      __syncthreads();
-      if (s_done) break;
+    for (int d = 32; d >= 1; d >>= 1) {
+      a &= shfl_xor_u64(a, d);
+      o |= shfl_xor_u64(o, d);
     }
-    T = s_prefix;  // keys are distinct: exactly k keys are >= T (the base of the last bin)
+    if (lane_id() == 0) {
+      s_and[threadIdx.x >> 6] = a;
+      s_or[threadIdx.x >> 6] = o;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      a &= s_and[w];
+      o |= s_or[w];
+    }
+    // keys are distinct, so they differ somewhere: bit hi is the highest
+    int hi = 63 - __builtin_clzll(a ^ o);
+    unsigned long long mask = hi == 63 ? 0 : ~0ull << (hi + 1);  // bits fixed so far
+    T = a & mask;
+    uint32_t rem = (uint32_t)k;
+    for (;;) {
+      const int shift = max(0, hi - 11);
+      for (int i = threadIdx.x; i < TOPK_BINS; i += TOPK_THREADS) hist[i] = 0;
+      __syncthreads();
+      each([&](unsigned long long K) {
+        if ((K & mask) == T) atomicAdd(&hist[(uint32_t)(K >> shift) & (TOPK_BINS - 1) & ((2u << (hi - shift)) - 1)], 1u);
+      });
+      __syncthreads();
+      find_bin<W, TOPK_BINS / TOPK_THREADS>(hist, rem, wsum, &s_bin);
+      const uint32_t bin = s_bin.x, here = hist[bin];
+      rem -= s_bin.y;
+      T |= (unsigned long long)bin << shift;
+      // the whole bin is needed: every key >= its base is taken (with every
+      // bit fixed a bin holds one key)
+      if (here == rem || shift == 0) break;
+      mask = ~0ull << shift;
+      hi = shift - 1;
+      __syncthreads();  // hist and s_bin are read above and written next
+    }
   }
   for (int i = threadIdx.x; i < kpow2; i += TOPK_THREADS) sk[i] = 0;
   if (threadIdx.x == 0) s_count = 0;
   __syncthreads();
-  for (int i = threadIdx.x; i < n; i += TOPK_THREADS) {
-    const unsigned long long K = pack_key(fh[i], (uint32_t)ci[i]);
+  each([&](unsigned long long K) {
     if (K >= T) {
       const int p = atomicAdd(&s_count, 1);
       if (p < kpow2) sk[p] = K;
     }
-  }
+  });
   __syncthreads();
   // bitonic sort, descending
   for (int size = 2; size <= kpow2; size <<= 1)

@@ -1,0 +1,43 @@
+"""The small batch's select (k_keep_list, k_keep_cut) and the top-k against the
+oracle, at the edges of their chunks (4096 documents), of the lists and of the
+registers: no more hits than candidates, one candidate, whole documents sets
+tied (the query's list overflows and F' is read instead), more entries than a
+thread keeps, and k of 1 up to every candidate."""
+import numpy as np
+import pytest
+import torch
+
+from util_gpu import check_search, q_tensor, say, setup
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("ndocs", [4095, 4096, 4097, 12_289])
+@pytest.mark.parametrize("ncand,k", [(1, 1), (37, 37), (4096, 100)])
+def test_chunk_edges(ndocs, ncand, k):
+    w, c, _, _, oi, idx = setup("tiny", ndocs=ndocs, ncent=256, len_kind=2, len_lo=1, len_hi=4)
+    q, _ = c.queries(3, 32, query_seed=ndocs + ncand)
+    cand, keys, nval = idx.prune(q_tensor(q, "bf16"), 4, ncand)
+    torch.cuda.synchronize()
+    ref = oi.prune(q, 4, min(ncand, ndocs))
+    for i in range(3):
+        n = ref["n_cand"][i]
+        order = np.argsort(ref["cand"][i, :n])
+        assert nval[i].item() == n
+        assert np.array_equal(cand[i, :n].cpu().numpy(), ref["cand"][i, :n][order])
+        assert np.array_equal(keys[i, :n].cpu().numpy(), ref["cand_keys"][i, :n][order])
+        assert (cand[i, n:] == -1).all()
+    check_search(idx, oi, q, 4, ncand, k, "bf16", f"{ndocs} documents, ncand {ncand}, k {k}")
+
+
+@pytest.mark.parametrize("ncand,k", [(10, 3), (20_000, 1), (20_000, 5000), (30_000, 8192)])
+def test_ties_and_long_lists(ncand, k):
+    """30,000 documents over 64 centroids: an all-zero query ties every hit at
+    F' = 0 and every score at 0, more than a list of 4 ncand + 4096 holds for
+    ncand = 10; with ncand = 20,000 the list (and the top-k's input) is longer
+    than the registers take."""
+    w, c, _, _, oi, idx = setup("tiny", ndocs=30_000, ncent=64, len_kind=2, len_lo=1, len_hi=3)
+    q, _ = c.queries(3, 8, query_seed=5)
+    q[1] = 0
+    say("ties", ncand, k)
+    check_search(idx, oi, q, 32, ncand, k, "bf16", f"ties, ncand {ncand}, k {k}")
