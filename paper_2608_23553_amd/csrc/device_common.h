@@ -68,6 +68,27 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
   return (uint32_t)v;
 }
 
+// Maximum over the 64 lanes of a wave, in every lane, by DPP moves.
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t x) {
+#define CHIMERA_MX64(CTRL, ROWS)                                                                              \
+  {                                                                                                           \
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, ROWS, 0xF, false);   \
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(x >> 32), CTRL, ROWS, 0xF, false);     \
+    const uint64_t y = (uint64_t)hi << 32 | lo;                                                               \
+    x = y > x ? y : x;                                                                                        \
+  }
+  CHIMERA_MX64(0x111, 0xF)  // row_shr:1, 2, 4, 8: lane 15 of each row of 16
+  CHIMERA_MX64(0x112, 0xF)
+  CHIMERA_MX64(0x114, 0xF)
+  CHIMERA_MX64(0x118, 0xF)
+  CHIMERA_MX64(0x142, 0xA)  // row_bcast:15 into rows 1, 3
+  CHIMERA_MX64(0x143, 0xC)  // row_bcast:31 into rows 2, 3
+#undef CHIMERA_MX64
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, 63);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), 63);
+  return (uint64_t)hi << 32 | lo;
+}
+
 // Exclusive prefix sum of x over a block of W waves and the total.  wsum [W]
 // is shared and free for the next call once every thread has passed a barrier
 // after this one.

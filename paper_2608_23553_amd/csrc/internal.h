@@ -94,6 +94,7 @@ void launch_check_queries(const void *Q, int q_dtype, int64_t ntokens, double li
                           hipStream_t s);
 
 // Probe: S = Qs * cent^T on MFMA, top-nprobe per row.  rows = nq*TQP.
+// cop is probe_operand's copy of the centroids (probe_operand_size values).
 // part: [nsplit][rows][pmax] u64 partial lists.  ST (optional): [nq][ncent][TQP] f32.
 struct ProbePlan {
   int pmax = 0, nsplit = 0, tiles_per_split = 0;
@@ -101,7 +102,9 @@ struct ProbePlan {
 };
 ProbePlan plan_probe(int64_t rows, int ncent, int nprobe);
 size_t probe_part_bytes(const ProbePlan &p, int64_t rows);
-void launch_probe(const uint16_t *Qs, int64_t rows, int TQP, const uint16_t *cent, int ncent,
+int64_t probe_operand_size(int ncent);
+void probe_operand(const uint16_t *cent, int ncent, uint16_t *out);
+void launch_probe(const uint16_t *Qs, int64_t rows, int TQP, const uint16_t *cop, int ncent,
                   const ProbePlan &p, int nprobe, uint64_t *part, float *ST, hipStream_t s);
 // Merge partial lists into cent_ids/cent_keys [nq][TQP][nprobe] (rows j < Tq).
 void launch_probe_merge(const uint64_t *part, int64_t nq, int Tq, int TQP, const ProbePlan &p, int nprobe,
@@ -233,6 +236,7 @@ struct chimera_index {
   int64_t ndocs = 0, ntok = 0, nnz = 0;
   int64_t device_bytes = 0;
   uint16_t *d_cent = nullptr;
+  uint16_t *d_cent_op = nullptr;  // centroids in the probe's operand order (probe_operand)
   uint16_t *d_cent16 = nullptr;  // centroids as fp16 [ncent][dim], or null (see f16_tokens_exact)
   int64_t *d_doc_off = nullptr;
   int32_t *d_cid = nullptr;

@@ -144,27 +144,43 @@ __device__ __forceinline__ void fold_tile(uint64_t (&L)[P], uint64_t (&K)[16]) {
   merge_top_desc<P>(L, K);
 }
 
+// The centroids as MFMA row operands: element i of lane l in step s of tile t,
+// at ((8 t + s) 64 + l) 8 + i, is dimension 64 (l / 32) + 8 s + i of centroid
+// 32 t + l % 32 (rows past the last centroid repeat it), so a step's operand
+// is one contiguous KB.  From rows of 256 bytes every load instruction touched
+// 64 cache lines, and the address units, not the matrix cores, bounded the
+// probe: 7.6 against 4.0 ms for 32,768 rows x 262,144 centroids (nprobe 16).
+void probe_operand(const uint16_t *cent, int ncent, uint16_t *out) {
+  const int64_t ntiles = (ncent + 31) / 32;
+  for (int64_t t = 0; t < ntiles; ++t)
+    for (int s = 0; s < 8; ++s)
+      for (int l = 0; l < 64; ++l) {
+        const int64_t c = std::min<int64_t>(32 * t + (l & 31), ncent - 1);
+        std::copy_n(cent + c * 128 + 64 * (l >> 5) + 8 * s, 8, out + ((8 * t + s) * 64 + l) * 8);
+      }
+}
+int64_t probe_operand_size(int ncent) { return (int64_t)((ncent + 31) / 32) * 4096; }
+
 // One workgroup: 32 query rows (one column block) x a range of centroid tiles.
 // Four waves stride over 32-centroid tiles; each wave computes a 32x32 tile
 // of S^T (rows = centroids, cols = query rows) with 8 MFMA 32x32x16 steps.
 // The contraction index k of MFMA step s, lane half h, element i is
 // dimension 64h + 8s + i for both operands (any common permutation of the
-// 128 dimensions gives the same exact sum), so every lane loads 128
-// contiguous bytes of its centroid row and of its query row.
+// 128 dimensions gives the same exact sum).
 // Each lane keeps the sorted top PMAX keys of the centroids it sees.  Early in
 // its stream nearly every key enters some lane's list, and a tile's 16 keys go
 // in at once through sorting networks (lists of 4 to 16); lists of 4 or 8
 // switch, once a lane has seen 128 * PMAX keys and entries have become rare,
 // to inserting keys one by one where they beat the list's last, as lists of
 // 32 and 64 do throughout.  With TAU, tau[row] is a lower bound on the row's
-// nprobe-th best key (from a sample of the centroids): keys below it can
-// never be selected and are dropped before they reach a list, so keys are
-// inserted one by one, and rarely.
+// nprobe-th best score (from a sample of the centroids): scores below it can
+// never be selected and are dropped by one comparison each, before a key is
+// made of them, so keys are inserted one by one, and rarely.
 template <int PMAX, int TQP, bool WRITE_ST, bool TAU>
-__global__ __launch_bounds__(256) void k_probe(const uint16_t *__restrict__ Qs, const uint16_t *__restrict__ cent,
+__global__ __launch_bounds__(256) void k_probe(const uint16_t *__restrict__ Qs, const uint4 *__restrict__ cop,
                                                int ncent, int tiles_per_split, int64_t rows,
                                                uint64_t *__restrict__ part, float *__restrict__ ST,
-                                               const uint64_t *__restrict__ tau) {
+                                               const float *__restrict__ tau) {
   __shared__ uint64_t lds[3][32][PMAX];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 31, h = lane >> 5;
@@ -180,7 +196,7 @@ __global__ __launch_bounds__(256) void k_probe(const uint16_t *__restrict__ Qs, 
   uint64_t L[PMAX];
 #pragma unroll
   for (int i = 0; i < PMAX; ++i) L[i] = 0;  // every real key is > 0
-  const uint64_t tr = TAU ? tau[qrow] : 0;
+  const float tr = TAU ? tau[qrow] : 0.f;
 
   const int ntiles = (ncent + 31) >> 5;
   const int t0 = split * tiles_per_split;
@@ -191,13 +207,12 @@ __global__ __launch_bounds__(256) void k_probe(const uint16_t *__restrict__ Qs, 
   if (WRITE_ST && split == 0 && wave == 0 && h == 0) ST[st_base + (int64_t)ncent * TQP] = -INFINITY;
 
   for (int t = t0 + wave; t < t1; t += 4) {
-    // rows past the last centroid repeat it; their scores are dropped below
-    const int crow = min(t * 32 + col, ncent - 1);
+    // (rows past the last centroid repeat it; their scores are dropped below)
     bf16x8 a[8];
     {
-      const uint4 *cp = (const uint4 *)(cent + (int64_t)crow * 128 + 64 * h);
+      const uint4 *cp = cop + (int64_t)t * 512 + lane;
 #pragma unroll
-      for (int s = 0; s < 8; ++s) a[s] = as_bf16x8(cp[s]);
+      for (int s = 0; s < 8; ++s) a[s] = as_bf16x8(cp[64 * s]);
     }
     __builtin_amdgcn_sched_barrier(0);  // the tile's 8 loads in flight together
     f32x16 acc;
@@ -241,9 +256,10 @@ __global__ __launch_bounds__(256) void k_probe(const uint16_t *__restrict__ Qs, 
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int c = cbase + 8 * (v >> 2) + (v & 3);
+        if (TAU && !(acc[v] >= tr)) continue;
         if (c < ncent) {
           const uint64_t K = pack_key(to_key(acc[v]), (uint32_t)c);
-          if (K >= tr && K > L[PMAX - 1]) insert_desc<PMAX>(L, K);
+          if (K > L[PMAX - 1]) insert_desc<PMAX>(L, K);
         }
       }
     }
@@ -288,96 +304,138 @@ static void plan_splits(int64_t rows, int ncent, int &nsplit, int &tiles_per_spl
   nsplit = (ntiles + tiles_per_split - 1) / tiles_per_split;
 }
 
+// With many centroids, the first 1/16 of them first give every row a lower
+// bound on its nprobe-th best score: the nprobe-th largest of the maxima of
+// 8 s_nsplit disjoint parts of the sample (at least 4 nprobe parts, so that
+// the bound is near the sample's own nprobe-th).  For 32,768 rows x 262,144
+// centroids the two launches take 0.24 ms (1.41 ms when the sample was probed
+// like the rest, its lists folded and the nprobe-th popped).  They pay where
+// there are many centroids, and for fewer where rows x centroids is large:
+// 2,048 rows x 16,384 centroids 73 -> 68 us, 8,192 rows 157 -> 101 us.
 ProbePlan plan_probe(int64_t rows, int ncent, int nprobe) {
   ProbePlan p;
   p.pmax = nprobe <= 4 ? 4 : nprobe <= 8 ? 8 : nprobe <= 16 ? 16 : nprobe <= 32 ? 32 : 64;
   plan_splits(rows, ncent, p.nsplit, p.tiles_per_split);
-  // with many centroids, the first 1/16 of them first give every row a lower
-  // bound on its nprobe-th best key
-  p.sample = ncent >= 65536 ? (ncent / 16 + 31) / 32 * 32 : 0;
-  if (p.sample) plan_splits(rows, p.sample, p.s_nsplit, p.s_tiles_per_split);
+  const int sample = (ncent / 16 + 31) / 32 * 32, stiles = sample / 32;
+  const int want = (nprobe + 1) / 2;  // splits for 4 nprobe parts
+  if ((ncent >= 65536 || (ncent >= 8192 && rows * ncent >= ((int64_t)1 << 25))) && want <= (stiles + 3) / 4) {
+    p.sample = sample;
+    plan_splits(rows, sample, p.s_nsplit, p.s_tiles_per_split);
+    if (p.s_nsplit < want) {
+      p.s_tiles_per_split = stiles / want;
+      p.s_nsplit = (stiles + p.s_tiles_per_split - 1) / p.s_tiles_per_split;
+    }
+  }
   return p;
 }
 
 size_t probe_part_bytes(const ProbePlan &p, int64_t rows) {
-  const int64_t ns = std::max(p.nsplit, p.sample ? p.s_nsplit : 0);
-  return (size_t)ns * rows * p.pmax * 8 + (p.sample ? (size_t)rows * 8 : 0);
+  return std::max((size_t)p.nsplit * rows * p.pmax * 8, (size_t)p.s_nsplit * 8 * rows * 4) +
+         (p.sample ? (size_t)rows * 8 : 0);
 }
 
-// Per row (one wave each): the nprobe-th best key over the partial lists of
-// nsplit splits, folded as k_probe_merge folds them.
-template <int PMAX>
-__global__ __launch_bounds__(256) void k_probe_tau(const uint64_t *__restrict__ part, int64_t rows, int nsplit,
-                                                   int nprobe, uint64_t *__restrict__ tau) {
+// Maxima over the sample's parts: a lane's tiles are a part, 8 per split (four
+// waves, two halves of 16 centroids a tile).  bound [8 s_nsplit][rows].
+__global__ __launch_bounds__(256) void k_probe_bound(const uint16_t *__restrict__ Qs, const uint4 *__restrict__ cop,
+                                                     int ntiles, int tiles_per_split, int64_t rows,
+                                                     float *__restrict__ bound) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 31, h = lane >> 5;
+  const int64_t qrow = (int64_t)blockIdx.x * 32 + col;
+  bf16x8 bq[8];
+  {
+    const uint4 *qp = (const uint4 *)(Qs + qrow * 128 + 64 * h);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) bq[s] = as_bf16x8(qp[s]);
+  }
+  const int t0 = blockIdx.y * tiles_per_split, t1 = min(ntiles, t0 + tiles_per_split);
+  float m = -INFINITY;
+  for (int t = t0 + wave; t < t1; t += 4) {
+    const uint4 *cp = cop + (int64_t)t * 512 + lane;
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(cp[64 * s]), bq[s], acc, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) m = fmaxf(fmaxf(m, acc[v]), acc[v + 1]);
+  }
+  bound[((int64_t)blockIdx.y * 8 + wave * 2 + h) * rows + qrow] = m;
+}
+
+// Per row (one wave each): the nprobe-th largest of its n <= 64 PER maxima.
+// -inf where there are fewer (nothing is dropped then).
+template <int PER>
+__global__ __launch_bounds__(256) void k_probe_tau(const float *__restrict__ bound, int64_t rows, int n, int nprobe,
+                                                   float *__restrict__ tau) {
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
-  uint64_t L[PMAX];
+  // order-preserving keys, distinct by the part's index in the low bits
+  uint64_t x[PER];
 #pragma unroll
-  for (int i = 0; i < PMAX; ++i) L[i] = 0;
-  for (int sp = lane; sp < nsplit; sp += 64) {
-    const uint64_t *src = part + ((int64_t)sp * rows + row) * PMAX;
-    for (int i = 0; i < PMAX; ++i) {
-      const uint64_t K = src[i];
-      if (K <= L[PMAX - 1]) break;
-      insert_desc<PMAX>(L, K);
-    }
+  for (int u = 0; u < PER; ++u) {
+    const int i = lane + 64 * u;
+    const uint32_t b = i < n ? __float_as_uint(bound[(int64_t)i * rows + row]) : 0xFF800000u;
+    x[u] = (uint64_t)(b & 0x80000000u ? ~b : b | 0x80000000u) << 32 | (uint32_t)(i + 1);
   }
   uint64_t best = 0;
   for (int r = 0; r < nprobe; ++r) {
-    best = L[0];
+    uint64_t m = x[0];
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-      const uint64_t o = shfl_xor_u64(best, m);
-      best = o > best ? o : best;
-    }
-    if (L[0] == best) {  // keys are unique: one lane owns the winner
+    for (int u = 1; u < PER; ++u) m = x[u] > m ? x[u] : m;
+    best = wave_max_u64(m);
 #pragma unroll
-      for (int i = 0; i < PMAX - 1; ++i) L[i] = L[i + 1];
-      L[PMAX - 1] = 0;
-    }
+    for (int u = 0; u < PER; ++u) x[u] = x[u] == best ? 0 : x[u];
   }
-  if (lane == 0) tau[row] = best;
+  if (lane == 0) {
+    const uint32_t k = (uint32_t)(best >> 32);
+    tau[row] = k ? __uint_as_float(k & 0x80000000u ? k & 0x7FFFFFFFu : ~k) : -INFINITY;
+  }
 }
 
 template <int P, int TQP>
-static void launch_probe_t(const uint16_t *Qs, int64_t rows, const uint16_t *cent, int ncent, const ProbePlan &p,
+static void launch_probe_t(const uint16_t *Qs, int64_t rows, const uint4 *cent, int ncent, const ProbePlan &p,
                            int nprobe, uint64_t *part, float *ST, hipStream_t s) {
-  uint64_t *tau = nullptr;
+  float *tau = nullptr;
   if (p.sample) {
-    // the sample's lists, then each row's bound
-    const int64_t ns = std::max(p.nsplit, p.s_nsplit);
-    tau = part + (size_t)ns * rows * P;
-    hipLaunchKernelGGL((k_probe<P, TQP, false, false>), dim3((unsigned)(rows / 32), (unsigned)p.s_nsplit), dim3(256),
-                       0, s, Qs, cent, p.sample, p.s_tiles_per_split, rows, part, (float *)nullptr,
-                       (const uint64_t *)nullptr);
-    hipLaunchKernelGGL((k_probe_tau<P>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, part, rows, p.s_nsplit,
-                       nprobe, tau);
+    // the sample's maxima (in the lists' place), then each row's bound
+    float *bound = (float *)part;
+    const int n = 8 * p.s_nsplit;
+    tau = (float *)((char *)part + probe_part_bytes(p, rows) - (size_t)rows * 8);
+    hipLaunchKernelGGL(k_probe_bound, dim3((unsigned)(rows / 32), (unsigned)p.s_nsplit), dim3(256), 0, s, Qs, cent,
+                       p.sample / 32, p.s_tiles_per_split, rows, bound);
+    const dim3 g((unsigned)((rows + 3) / 4)), b(256);
+    if (n <= 64) hipLaunchKernelGGL(k_probe_tau<1>, g, b, 0, s, bound, rows, n, nprobe, tau);
+    else if (n <= 256) hipLaunchKernelGGL(k_probe_tau<4>, g, b, 0, s, bound, rows, n, nprobe, tau);
+    else if (n <= 1024) hipLaunchKernelGGL(k_probe_tau<16>, g, b, 0, s, bound, rows, n, nprobe, tau);
+    else hipLaunchKernelGGL(k_probe_tau<64>, g, b, 0, s, bound, rows, n, nprobe, tau);
   }
   dim3 grid((unsigned)(rows / 32), (unsigned)p.nsplit);
   if (ST && tau)
     hipLaunchKernelGGL((k_probe<P, TQP, true, true>), grid, dim3(256), 0, s, Qs, cent, ncent, p.tiles_per_split, rows,
-                       part, ST, (const uint64_t *)tau);
+                       part, ST, (const float *)tau);
   else if (ST)
     hipLaunchKernelGGL((k_probe<P, TQP, true, false>), grid, dim3(256), 0, s, Qs, cent, ncent, p.tiles_per_split, rows,
-                       part, ST, (const uint64_t *)nullptr);
+                       part, ST, (const float *)nullptr);
   else if (tau)
     hipLaunchKernelGGL((k_probe<P, TQP, false, true>), grid, dim3(256), 0, s, Qs, cent, ncent, p.tiles_per_split, rows,
-                       part, ST, (const uint64_t *)tau);
+                       part, ST, (const float *)tau);
   else
     hipLaunchKernelGGL((k_probe<P, TQP, false, false>), grid, dim3(256), 0, s, Qs, cent, ncent, p.tiles_per_split,
-                       rows, part, ST, (const uint64_t *)nullptr);
+                       rows, part, ST, (const float *)nullptr);
 }
 
 template <int P>
-static void launch_probe_p(const uint16_t *Qs, int64_t rows, int TQP, const uint16_t *cent, int ncent,
+static void launch_probe_p(const uint16_t *Qs, int64_t rows, int TQP, const uint4 *cent, int ncent,
                            const ProbePlan &p, int nprobe, uint64_t *part, float *ST, hipStream_t s) {
   if (TQP == 32) launch_probe_t<P, 32>(Qs, rows, cent, ncent, p, nprobe, part, ST, s);
   else launch_probe_t<P, 64>(Qs, rows, cent, ncent, p, nprobe, part, ST, s);
 }
 
-void launch_probe(const uint16_t *Qs, int64_t rows, int TQP, const uint16_t *cent, int ncent, const ProbePlan &p,
+void launch_probe(const uint16_t *Qs, int64_t rows, int TQP, const uint16_t *cop, int ncent, const ProbePlan &p,
                   int nprobe, uint64_t *part, float *ST, hipStream_t s) {
+  const uint4 *cent = (const uint4 *)cop;
   switch (p.pmax) {
     case 4: launch_probe_p<4>(Qs, rows, TQP, cent, ncent, p, nprobe, part, ST, s); break;
     case 8: launch_probe_p<8>(Qs, rows, TQP, cent, ncent, p, nprobe, part, ST, s); break;
@@ -405,23 +463,30 @@ __global__ __launch_bounds__(256) void k_probe_merge(const uint64_t *__restrict_
   uint64_t L[PMAX];
 #pragma unroll
   for (int i = 0; i < PMAX; ++i) L[i] = 0;
-  for (int sp = lane; sp < nsplit; sp += 64) {
-    const uint64_t *src = part + ((int64_t)sp * rows + row) * PMAX;
-    for (int i = 0; i < PMAX; ++i) {
-      const uint64_t K = src[i];
-      if (K <= L[PMAX - 1]) break;
-      insert_desc<PMAX>(L, K);
+  // the lists' first keys are loaded together: most lists have no key left
+  // that counts
+  for (int s0 = lane; s0 < nsplit; s0 += 64 * 8) {
+    uint64_t head[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      head[u] = s0 + 64 * u < nsplit ? part[((int64_t)(s0 + 64 * u) * rows + row) * PMAX] : 0;
+#pragma unroll 1
+    for (int u = 0; u < 8; ++u) {
+      uint64_t K = head[0];
+#pragma unroll
+      for (int i = 0; i < 7; ++i) head[i] = head[i + 1];
+      const uint64_t *src = part + ((int64_t)(s0 + 64 * u) * rows + row) * PMAX;
+      for (int i = 1; K > L[PMAX - 1]; ++i) {
+        insert_desc<PMAX>(L, K);
+        if (i == PMAX) break;
+        K = src[i];
+      }
     }
   }
   int32_t *oi = cent_ids + row * nprobe;
   int32_t *ok = cent_keys + row * nprobe;
   for (int r = 0; r < nprobe; ++r) {
-    uint64_t best = L[0];
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-      const uint64_t o = shfl_xor_u64(best, m);
-      best = o > best ? o : best;
-    }
+    const uint64_t best = wave_max_u64(L[0]);
     // keys are unique (distinct ids), so exactly one lane owns the winner
     if (L[0] == best) {
 #pragma unroll
@@ -429,8 +494,10 @@ __global__ __launch_bounds__(256) void k_probe_merge(const uint64_t *__restrict_
       L[PMAX - 1] = 0;
     }
     if (lane == 0) {
-      oi[r] = (int32_t)key_id(best);
-      ok[r] = key_score(best);
+      // (a row whose scores are not numbers may be left without keys: its
+      // lists are then the first centroids at score 0)
+      oi[r] = best ? (int32_t)key_id(best) : r;
+      ok[r] = best ? key_score(best) : 0;
     }
   }
 }
