@@ -238,8 +238,8 @@ static size_t carve_bytes(const chimera_index *idx, int64_t nb, int TQP, int npr
   b += align_up(probe_part_bytes(plan, rows));                 // partial lists
   b += 2 * align_up((size_t)rows * nprobe * 4);                // cent ids / keys
   if (stop >= STOP_FULL && !rq && !by_doc) b += align_up((size_t)nb * (idx->ncent + 1) * TQP * 4);  // S^T + sentinel rows
-  if (by_doc) b += align_up(doc_score_scratch_bytes(nb, TQP, idx->ndocs, ncand));  // visits by document
-  if (rq) b += align_up((size_t)rows * RQ_ROW_BYTES) + align_up((size_t)rows * 4);  // query limbs, qsum
+  if (by_doc) b += align_up(doc_score_scratch_bytes(nb, TQP, idx->ndocs, ncand, rq));  // visits by document
+  if (rq && !by_doc) b += align_up((size_t)rows * RQ_ROW_BYTES) + align_up((size_t)rows * 4);  // query limbs, qsum
   if (stop >= STOP_CANDIDATES) {
     b += align_up((size_t)nb * idx->ndocs * 4);  // F'
     b += align_up((size_t)nb * 4097 * 4);        // select histogram and list length
@@ -353,7 +353,7 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
   };
   // scoring by document where a sub-batch's candidates overlap enough
   // (k_score_docs.hip), by query otherwise
-  bool by_doc = stop == STOP_FULL && !o.rabitq && idx->d_cent16;
+  bool by_doc = stop == STOP_FULL && (o.rabitq || idx->d_cent16);
   int64_t B = largest_for(by_doc);
   if (by_doc && !doc_score_grouped(B, idx->ndocs, idx->ntok, idx->ndense, ncand)) {
     by_doc = false;
@@ -480,7 +480,7 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
     if (stop == STOP_PRUNE) continue;
     // RaBitQ scoring: the rotated queries as int8 limbs
     RqQuery rq;
-    if (o.rabitq) {
+    if (o.rabitq && !by_doc) {
       rq.Qi8 = cv.take<uint8_t>((size_t)rows * RQ_ROW_BYTES);
       rq.qsum = cv.take<float>((size_t)rows);
       if (cv.off > scratch_cap) return fail(CHIMERA_E_NOMEM, "internal: scratch plan overflow");
@@ -493,11 +493,16 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
       continue;
     }
     stage_mark(idx, s, mark);
-    if (o.rabitq) {
+    if (o.rabitq && by_doc) {
+      char *w = cv.take<char>(doc_score_scratch_bytes(nb, TQP, idx->ndocs, ncand, true));
+      if (cv.off > scratch_cap) return fail(CHIMERA_E_NOMEM, "internal: scratch plan overflow");
+      launch_doc_score_rq(Qs, nb, Tq, TQP, idx->d_rq_signs, idx->d_doc_off, idx->d_rq_bits, idx->d_rq_g1, idx->ndocs,
+                          cand, nval, ncand, w, fhat, s);
+    } else if (o.rabitq) {
       launch_rq_score(rq.Qi8, rq.qsum, nb, TQP, idx->d_doc_off, idx->d_rq_bits, idx->d_rq_g1, cand, nval,
                       ncand, 0, ncand, fhat, s);
     } else if (by_doc) {
-      char *w = cv.take<char>(doc_score_scratch_bytes(nb, TQP, idx->ndocs, ncand));
+      char *w = cv.take<char>(doc_score_scratch_bytes(nb, TQP, idx->ndocs, ncand, false));
       if (cv.off > scratch_cap) return fail(CHIMERA_E_NOMEM, "internal: scratch plan overflow");
       launch_doc_score(Qs, nb, Tq, TQP, idx->d_cent16, idx->d_doc_off, idx->d_cid, idx->d_codes, idx->nbits,
                        idx->h_weights, idx->ndocs, cand, nval, ncand, w, fhat, s);

@@ -173,11 +173,17 @@ void launch_residual_score(const uint16_t *Qs, int64_t nq, int Tq, int TQP, cons
 bool f16_tokens_exact(const uint16_t *cent, int64_t n, const uint16_t *weights, int nweights);
 void f16_of_bf16_grid(const uint16_t *src, int64_t n, uint16_t *dst);
 bool doc_score_grouped(int64_t nq, int64_t ndocs, int64_t ntok, int ndense, int ncand);
-size_t doc_score_scratch_bytes(int64_t nq, int TQP, int64_t ndocs, int ncand);
+size_t doc_score_scratch_bytes(int64_t nq, int TQP, int64_t ndocs, int ncand, bool rq);
 void launch_doc_score(const uint16_t *Qs, int64_t nq, int Tq, int TQP, const uint16_t *cent16,
                       const int64_t *doc_off, const int32_t *cid, const uint8_t *codes, int nbits,
                       const uint16_t *weights_host, int64_t ndocs, const int32_t *cand_ids, const int32_t *n_valid,
                       int ncand, void *scratch, int32_t *fhat, hipStream_t s);
+
+// The same from the RaBitQ 1-bit codes, in place of launch_rq_prep and
+// launch_rq_score (bits, g1 as there).
+void launch_doc_score_rq(const uint16_t *Qs, int64_t nq, int Tq, int TQP, const int8_t *signs, const int64_t *doc_off,
+                         const uint8_t *bits, const float *g1, int64_t ndocs, const int32_t *cand_ids,
+                         const int32_t *n_valid, int ncand, void *scratch, int32_t *fhat, hipStream_t s);
 
 // RaBitQ document scoring (k_rabitq.hip).  Query preparation: for each of
 // the rows rounded query rows Qs [rows][128], X = 2048 H diag(signs) q as

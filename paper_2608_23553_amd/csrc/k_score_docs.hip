@@ -471,13 +471,268 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   }
 }
 
+// ------------------------------------------------------------ RaBitQ scoring
+// The same from the 1-bit RaBitQ codes (k_rabitq.hip has the formula): a
+// document's bits become fp16 zeros and ones in LDS once, and a visiting
+// query's rotated token x is the sum of two fp16 values, hi = fp16(x) and lo =
+// x - hi, both exact (x is a multiple of 2^-11 below 32 in magnitude for
+// tokens of norm below 2.8, so hi rounds at 2^-6 or finer and lo has at most 5
+// bits).  Their products with the bits add up in one fp32 accumulator that
+// starts at -sum(x) / 2: <x, b> - sum(x) / 2 is a multiple of 2^-12 below 2^12,
+// exact in any order.  One multiply by the token's factor g1 is the one
+// rounding, as before.  With the document's tokens as rows, the maximum over
+// tokens stays in a lane's registers.  Going query by query, the bits were
+// expanded for every visit and the three 7-bit limbs of X chained by shifts:
+// 12 int8 MFMA and about 250 vector instructions per 32 x 32 tile, the latter
+// the bound; here 16 MFMA and 24, and the 16 KB of a visit's operand take as
+// long to load (64 bytes per clock and CU).  256 queries of 4096 candidates on
+// 20,000 documents of 64 tokens: 1500 us against 1859 us.
+
+// One wave per query row: x = H diag(signs) q by the fast transform in fp32
+// (lane l holds dimensions 2l and 2l + 1), its hi and lo parts in operand
+// order (block q * NCB + cb: 512 groups of hi, then 512 of lo), and sum(x) / 2.
+__global__ __launch_bounds__(256) void k_rq_operand(const uint16_t *__restrict__ Qs, int64_t rows,
+                                                    const int8_t *__restrict__ signs, uint16_t *__restrict__ Qf,
+                                                    float *__restrict__ half_sum) {
+  const int lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  const uint32_t w = ((const uint32_t *)(Qs + row * 128))[lane];
+  float x0 = __uint_as_float(w << 16) * (float)signs[2 * lane];
+  float x1 = __uint_as_float(w & 0xFFFF0000u) * (float)signs[2 * lane + 1];
+  const float a = x0 + x1, b = x0 - x1;
+  x0 = a;
+  x1 = b;
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) {
+    const float y0 = __shfl_xor(x0, m, 64), y1 = __shfl_xor(x1, m, 64);
+    x0 = lane & m ? y0 - x0 : x0 + y0;
+    x1 = lane & m ? y1 - x1 : x1 + y1;
+  }
+  const _Float16 h0 = (_Float16)x0, h1 = (_Float16)x1;
+  const _Float16 l0 = (_Float16)(x0 - (float)h0), l1 = (_Float16)(x1 - (float)h1);
+  // dimensions 2l, 2l + 1: half d / 64, step d % 64 / 8, element d % 8
+  const int d = 2 * lane;
+  uint32_t *o = (uint32_t *)(Qf + (row >> 5) * 8192 + ((d & 63) >> 3) * 512 + (32 * (d >> 6) + (int)(row & 31)) * 8 + (d & 7));
+  o[0] = (uint32_t)__builtin_bit_cast(uint16_t, h0) | (uint32_t)__builtin_bit_cast(uint16_t, h1) << 16;
+  o[2048] = (uint32_t)__builtin_bit_cast(uint16_t, l0) | (uint32_t)__builtin_bit_cast(uint16_t, l1) << 16;
+  float sum = x0 + x1;
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, 64);
+  if (lane == 0) half_sum[row] = 0.5f * sum;
+}
+
+// Bundles and jobs as k_doc_score; a job is one visit, its column blocks one
+// after the other.
+template <int NCB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_doc_score_rq(
+    const uint16_t *__restrict__ Qf, const float *__restrict__ half_sum, int Tq, int ncand,
+    const int64_t *__restrict__ doc_off, const uint8_t *__restrict__ bits, const float *__restrict__ g1, int64_t ndocs,
+    int ndb, const uint32_t *__restrict__ cnt, const uint32_t *__restrict__ first, const uint32_t *__restrict__ visit,
+    int32_t *__restrict__ fhat) {
+  constexpr int TL = 6, MAXU = 3;
+  constexpr int JW = NCB == 1 ? 2 : 1;            // visits per wave of a long document at a time
+  __shared__ f16x8 At[TL * 8 * 64];               // [tile][step][lane]
+  __shared__ __align__(16) float gt[TL * 32];     // the rows' factors
+  __shared__ float run[4][JW * NCB][32];
+  const int lane = threadIdx.x & 63, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t d = (int64_t)blockIdx.x * ndb + lane;
+  int nv = 0, nt = 0, len = 0, vo = 0;
+  int64_t beg = 0;
+  if (lane < ndb && d < ndocs) nv = (int)cnt[d];
+  if (nv > 0) {
+    vo = (int)first[d];
+    beg = doc_off[d];
+    len = (int)(doc_off[d + 1] - beg);
+    nt = (len + 31) >> 5;
+  }
+  unsigned long long todo = __ballot(nv > 0 && len > 0);
+
+  // (as k_doc_score: units of half a tile, loads before the barrier)
+  auto decode = [&](bool mine, int ts, int n, int t0, int T) {
+    uint32_t w[MAXU];
+    float g[MAXU];
+#pragma unroll
+    for (int k = 0; k < MAXU; ++k) {
+      const int u = wave + 4 * k;
+      w[k] = 0;
+      g[k] = 0.f;
+      if (u >= 2 * T) continue;  // wave-uniform
+      const int t = u >> 1;
+      const int e = __builtin_ctzll(__ballot(mine && ts <= t && t < ts + n));
+      const int row = 32 * (t0 + t - rl(ts, e)) + (lane & 31);
+      const int64_t tok = rl64(beg, e) + min(row, rl(len, e) - 1);
+      // steps 4 sh .. 4 sh + 3: dimensions 64 h + 32 sh .. + 31
+      w[k] = *(const uint32_t *)(bits + tok * 16 + 8 * h + 4 * (u & 1));
+      g[k] = g1[tok];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < MAXU; ++k) {
+      const int u = wave + 4 * k, sh = u & 1;
+      if (u >= 2 * T) continue;
+      f16x8 *out = At + ((u >> 1) * 8 + 4 * sh) * 64 + lane;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const uint32_t y = w[k] >> (8 * s);
+        uint4 x;  // bit i of the byte as fp16 0 or 1
+        x.x = (y & 1u) * 0x3C00u | (y >> 1 & 1u) * 0x3C000000u;
+        x.y = (y >> 2 & 1u) * 0x3C00u | (y >> 3 & 1u) * 0x3C000000u;
+        x.z = (y >> 4 & 1u) * 0x3C00u | (y >> 5 & 1u) * 0x3C000000u;
+        x.w = (y >> 6 & 1u) * 0x3C00u | (y >> 7 & 1u) * 0x3C000000u;
+        out[64 * s] = __builtin_bit_cast(f16x8, x);
+      }
+      if (sh == 0 && h == 0) gt[32 * (u >> 1) + lane] = g[k];
+    }
+    __syncthreads();
+  };
+  // Largest estimate of each of a block's 32 columns over tile slots ta .. tb
+  // - 1, in both half waves; g is the block's first group of Qf.
+  auto block_max = [&](uint32_t g, float hs, int ta, int tb) {
+    f16x8 b0[8], b1[8];
+    const f16x8 *gp = (const f16x8 *)Qf + g + lane;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      b0[s] = gp[64 * s];
+      b1[s] = gp[512 + 64 * s];
+    }
+    float m = -INFINITY;
+    for (int t = ta; t < tb; ++t) {
+      const f16x8 *a = At + t * 512 + lane;
+      f32x16 x;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) x[v] = -hs;
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        const f16x8 av = a[64 * s];
+        x = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, b0[s], x, 0, 0, 0);
+        x = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, b1[s], x, 0, 0, 0);
+      }
+#pragma unroll
+      for (int v = 0; v < 16; v += 4) {
+        // registers v .. v + 3 hold rows 8 (v / 4) + 4 h .. + 3
+        const float4 gv = *(const float4 *)(gt + 32 * t + 2 * v + 4 * h);
+        m = fmaxf(fmaxf(m, gv.x * x[v]), gv.y * x[v + 1]);
+        m = fmaxf(fmaxf(m, gv.z * x[v + 2]), gv.w * x[v + 3]);
+      }
+    }
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+    return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+  };
+  // the columns' keys rint(m 2^22) summed in two 32-bit halves (a key is below
+  // 2^40 in magnitude), in lane 31
+  auto key_sum = [&](const float (&m)[NCB]) {
+    long long total = 0;
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) {
+      const float r = rintf(m[cb] * KEY_SCALE), hi = floorf(r * (1.0f / 65536.0f));
+      const bool in = 32 * cb + (lane & 31) < Tq;
+      const int sh = ds_half_sum(in ? (int)hi : 0), sl = ds_half_sum(in ? (int)(r - hi * 65536.0f) : 0);
+      total += (long long)sh * 65536 + sl;
+    }
+    return (int32_t)std::min<long long>(INT32_MAX, std::max<long long>(-INT32_MAX, total));
+  };
+
+  while (todo) {
+    const int e0 = __builtin_ctzll(todo);
+    const int nt0 = rl(nt, e0);
+    if (nt0 > TL) {  // a long document, in pieces
+      todo &= todo - 1;
+      const int J = rl(nv, e0);
+      const uint32_t v0 = (uint32_t)rl(vo, e0);
+      for (int jb = 0; jb < J; jb += 4 * JW) {
+        for (int t0 = 0; t0 < nt0; t0 += TL) {
+          const int T = min(TL, nt0 - t0);
+          decode(lane == e0, 0, T, t0, T);
+          for (int i = 0; i < JW; ++i) {
+            const int jx = jb + wave + 4 * i;
+            if (jx >= J) break;
+            const uint32_t p = visit[v0 + jx], q = p / (uint32_t)ncand;
+            float m[NCB];
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) {
+              m[cb] = block_max((q * NCB + cb) * 1024, half_sum[(q * NCB + cb) * 32 + (lane & 31)], 0, T);
+              float *r = &run[wave][i * NCB + cb][lane & 31];
+              if (t0 > 0) m[cb] = fmaxf(m[cb], *r);
+              if (t0 + TL < nt0) *r = m[cb];
+            }
+            if (t0 + TL >= nt0) {
+              const int32_t key = key_sum(m);
+              if (lane == 31) fhat[p] = key;
+            }
+          }
+        }
+      }
+      continue;
+    }
+    bool mine = false;
+    int ts = 0, js = 0, T = 0, J = 0;
+    unsigned long long m = todo;
+    while (m) {
+      const int e = __builtin_ctzll(m);
+      const int te = rl(nt, e), je = rl(nv, e);
+      if (T + te > TL) break;
+      mine = lane == e ? true : mine;
+      ts = lane == e ? T : ts;
+      js = lane == e ? J : js;
+      T += te;
+      J += je;
+      m &= m - 1;
+    }
+    todo = m;
+    decode(mine, ts, nt, 0, T);
+    for (int jx = wave; jx < J; jx += 4) {
+      const int e = __builtin_ctzll(__ballot(mine && js <= jx && jx < js + nv));
+      const uint32_t p = visit[(uint32_t)rl(vo, e) + (uint32_t)(jx - rl(js, e))], q = p / (uint32_t)ncand;
+      const int ta = rl(ts, e), tb = ta + rl(nt, e);
+      float mm[NCB];
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb)
+        mm[cb] = block_max((q * NCB + cb) * 1024, half_sum[(q * NCB + cb) * 32 + (lane & 31)], ta, tb);
+      const int32_t key = key_sum(mm);
+      if (lane == 31) fhat[p] = key;
+    }
+  }
+}
+
 // ------------------------------------------------------------------ host
 static int64_t visit_docs(int64_t ndocs) { return (ndocs + VISIT_SEG - 1) / VISIT_SEG * VISIT_SEG; }
 
-// Scratch: the query operand, a count and a first visit per document (whole
-// segments) with the running total, and the visits.
-size_t doc_score_scratch_bytes(int64_t nq, int TQP, int64_t ndocs, int ncand) {
-  return (size_t)nq * TQP * 256 + (size_t)(2 * visit_docs(ndocs) + 64) * 4 + (size_t)nq * ncand * 4 + 1024;
+// Scratch: the query operand (256 bytes a row, 516 for RaBitQ's two parts and
+// sums), a count and a first visit per document (whole segments) with the
+// running total, and the visits.
+size_t doc_score_scratch_bytes(int64_t nq, int TQP, int64_t ndocs, int ncand, bool rq) {
+  return (size_t)nq * TQP * (rq ? 516 : 256) + (size_t)(2 * visit_docs(ndocs) + 64) * 4 + (size_t)nq * ncand * 4 + 1024;
+}
+
+// Sorts the visits of the kept candidates by document; ranks are taken in
+// fhat, which the scoring writes afterwards.
+struct Visits {
+  uint32_t *cnt, *first, *visit;
+  unsigned blocks;  // workgroups of ndb documents each
+  int ndb;
+};
+static Visits sort_visits(int64_t nq, int64_t ndocs, const int32_t *cand_ids, const int32_t *n_valid, int ncand,
+                          uint32_t *scratch, int32_t *fhat, hipStream_t s) {
+  const int64_t nd = visit_docs(ndocs);
+  Visits V;
+  V.cnt = scratch;
+  uint32_t *total = V.cnt + nd;
+  V.first = total + 64;
+  V.visit = V.first + nd;
+  const dim3 gv((unsigned)((ncand + 255) / 256), (unsigned)nq);
+  launch_fill_zero(V.cnt, (size_t)(nd + 64) * 4, s);
+  hipLaunchKernelGGL(k_visit_count, gv, dim3(256), 0, s, cand_ids, n_valid, ncand, V.cnt, (uint32_t *)fhat);
+  hipLaunchKernelGGL(k_visit_alloc, dim3((unsigned)(nd / VISIT_SEG)), dim3(256), 0, s, V.cnt, V.first, total);
+  hipLaunchKernelGGL(k_visit_fill, gv, dim3(256), 0, s, cand_ids, n_valid, ncand, V.first, (const uint32_t *)fhat,
+                     V.visit);
+  // documents per workgroup: 64, fewer while that leaves under about 6144
+  // workgroups
+  V.ndb = 64;
+  while (V.ndb > 1 && (ndocs + V.ndb - 1) / V.ndb < 6144) V.ndb >>= 1;
+  V.blocks = (unsigned)((ndocs + V.ndb - 1) / V.ndb);
+  return V;
 }
 
 // Scoring by document pays once the visits per document cover its decoding
@@ -502,35 +757,40 @@ void launch_doc_score(const uint16_t *Qs, int64_t nq, int Tq, int TQP, const uin
                       const uint16_t *weights_host, int64_t ndocs, const int32_t *cand_ids, const int32_t *n_valid,
                       int ncand, void *scratch, int32_t *fhat, hipStream_t s) {
   if (nq <= 0 || ncand <= 0) return;
-  const int64_t nd = visit_docs(ndocs);
   uint16_t *Qf = (uint16_t *)scratch;
-  uint32_t *cnt = (uint32_t *)(Qf + (size_t)nq * TQP * 128);
-  uint32_t *total = cnt + nd, *first = total + 64, *visit = first + nd;
   uint32_t w[8] = {0};
   const int B = 1 << nbits;
   for (int u = 0; u < B; ++u)
     w[u >> 1] |= (uint32_t)f16_of_grid_k(grid_k_of_float(float_of_bf16(weights_host[u]))) << (16 * (u & 1));
   const uint4 w_lo = make_uint4(w[0], w[1], w[2], w[3]), w_hi = make_uint4(w[4], w[5], w[6], w[7]);
   const int64_t n8 = nq * TQP * 16;
-  const dim3 gv((unsigned)((ncand + 255) / 256), (unsigned)nq);
   hipLaunchKernelGGL(k_query_operand, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s, Qs, n8, Qf);
-  launch_fill_zero(cnt, (size_t)(nd + 64) * 4, s);
-  hipLaunchKernelGGL(k_visit_count, gv, dim3(256), 0, s, cand_ids, n_valid, ncand, cnt, (uint32_t *)fhat);
-  hipLaunchKernelGGL(k_visit_alloc, dim3((unsigned)(nd / VISIT_SEG)), dim3(256), 0, s, cnt, first, total);
-  hipLaunchKernelGGL(k_visit_fill, gv, dim3(256), 0, s, cand_ids, n_valid, ncand, first, (const uint32_t *)fhat, visit);
-  // documents per workgroup: 64, fewer while that leaves under about 6144
-  // workgroups
-  int ndb = 64;
-  while (ndb > 1 && (ndocs + ndb - 1) / ndb < 6144) ndb >>= 1;
-  const dim3 grid((unsigned)((ndocs + ndb - 1) / ndb));
-#define CHIMERA_DS(NB, NC)                                                                                           \
-  hipLaunchKernelGGL((k_doc_score<NB, NC>), grid, dim3(256), 0, s, Qf, Tq, ncand, cent16, doc_off, cid, codes, w_lo, \
-                     w_hi, ndocs, ndb, cnt, first, visit, fhat)
+  const Visits V = sort_visits(nq, ndocs, cand_ids, n_valid, ncand, (uint32_t *)(Qf + (size_t)nq * TQP * 128), fhat, s);
+#define CHIMERA_DS(NB, NC)                                                                                            \
+  hipLaunchKernelGGL((k_doc_score<NB, NC>), dim3(V.blocks), dim3(256), 0, s, Qf, Tq, ncand, cent16, doc_off, cid, codes, \
+                     w_lo, w_hi, ndocs, V.ndb, V.cnt, V.first, V.visit, fhat)
   if (nbits == 2 && TQP == 32) CHIMERA_DS(2, 1);
   else if (nbits == 2) CHIMERA_DS(2, 2);
   else if (TQP == 32) CHIMERA_DS(4, 1);
   else CHIMERA_DS(4, 2);
 #undef CHIMERA_DS
+}
+
+void launch_doc_score_rq(const uint16_t *Qs, int64_t nq, int Tq, int TQP, const int8_t *signs, const int64_t *doc_off,
+                         const uint8_t *bits, const float *g1, int64_t ndocs, const int32_t *cand_ids,
+                         const int32_t *n_valid, int ncand, void *scratch, int32_t *fhat, hipStream_t s) {
+  if (nq <= 0 || ncand <= 0) return;
+  const int64_t rows = nq * TQP;
+  uint16_t *Qf = (uint16_t *)scratch;
+  float *half_sum = (float *)(Qf + (size_t)rows * 256);
+  hipLaunchKernelGGL(k_rq_operand, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, Qs, rows, signs, Qf, half_sum);
+  const Visits V = sort_visits(nq, ndocs, cand_ids, n_valid, ncand, (uint32_t *)(half_sum + rows), fhat, s);
+  if (TQP == 32)
+    hipLaunchKernelGGL((k_doc_score_rq<1>), dim3(V.blocks), dim3(256), 0, s, Qf, half_sum, Tq, ncand, doc_off, bits, g1,
+                       ndocs, V.ndb, V.cnt, V.first, V.visit, fhat);
+  else
+    hipLaunchKernelGGL((k_doc_score_rq<2>), dim3(V.blocks), dim3(256), 0, s, Qf, half_sum, Tq, ncand, doc_off, bits, g1,
+                       ndocs, V.ndb, V.cnt, V.first, V.visit, fhat);
 }
 
 }  // namespace chimera

@@ -9,10 +9,12 @@ import pytest
 import torch
 
 import oracle
+import synth
 from paper_2608_23553_amd import build_index
 from synth import k_to_bf16_bits
 from util_corpus import rand_grid
-from util_gpu import check_search, say, setup
+from util_build import product_builder
+from util_gpu import check_search, q_tensor, say, setup
 
 pytestmark = pytest.mark.gpu
 
@@ -45,3 +47,22 @@ def test_tokens_past_fp16_are_scored_by_query():
     say("axis centroid")
     check_search(idx, oi, q, 16, 300, 40, "bf16", "axis centroid")
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("Tq,lo,hi", [(5, 1, 80), (32, 31, 65), (32, 150, 300), (64, 120, 260)])
+def test_rabitq_by_document(Tq, lo, hi):
+    """The RaBitQ 1-bit scores of the same kind of batch; sampled queries."""
+    w, c, k, cl, oi, _ = setup("tiny", ndocs=300, ncent=64, len_kind=2, len_lo=lo, len_hi=hi)
+    signs = synth.rotation_signs(29)
+    idx = product_builder(c, w.nbits, rabitq_signs=signs).upload(0)
+    codes, _, g1 = oracle.rabitq_encode(k, signs, 4)
+    q, _ = c.queries(300, Tq, query_seed=Tq + hi)
+    q[3] = 0
+    say("rabitq by document", Tq, lo, hi)
+    ids, scores = idx.search_rabitq(q_tensor(q, "bf16"), 16, 300, 40)
+    torch.cuda.synchronize()
+    for i in (0, 3, 150, 299):
+        ref = oracle.search_rabitq(oi, q[i:i + 1], 16, 300, 40, signs, 4, codes, g1)
+        assert np.array_equal(ids[i].cpu().numpy(), ref["ids"][0]), i
+        assert np.array_equal(scores[i].cpu().numpy(), ref["scores"][0]), i
+    idx.close()
