@@ -34,7 +34,26 @@ void launch_fill_zero(void *p, size_t bytes, hipStream_t s) {
 }
 
 // Workgroup (query q, group g): the document ranges [d0, d0 + R) of a
-// contiguous group of ranges, one after the other.  The state of a range
+// contiguous group of ranges, one after the other, in one of two ways.
+//
+// Through chains and a table, where the query has at most WALK_TAB_BITS dense
+// groups (below): F' is a maximum per query token, so it needs no order.  The
+// dense groups' own F' is a table of 2^g sums, built once per workgroup, that
+// a document looks up by the bits of its dense mask.  Every posting entry of
+// the range is linked into its document's chain in LDS; documents with a chain
+// (about a quarter on Zipf-popular corpora) are listed and taken one a lane:
+// up to four entries are sorted by rank and each corrects the table's sum for
+// the tokens that no better entry or dense group holds; longer chains are
+// taken by the whole wave, a query token a lane.  Two barriers a range, where
+// the other way has one a rank and more; the group's histogram is kept in LDS
+// and added once.  1024 queries x 2.2M documents, 16 ranks: 23.8 -> 20.3 ms; 1M
+// documents, 8 ranks: 10.0 ms either way (10.8 rank by rank in this kernel,
+// whose registers are cut to 128 for two workgroups a CU).  The limit is now
+// the instructions and LDS round trips of each range (the VALU is busy 44% of
+// the time, the address units a third).
+//
+// Rank by rank, else, and from the first range on that holds more entries than
+// the chains take (WALK_NODES).  The state of a range
 // (per document: the mask of query tokens already credited, and F') lives in
 // LDS, so the updates are LDS atomics and each document's F' is written to
 // HBM once.  Query tokens that probe the same centroid at the same rank form
@@ -70,6 +89,12 @@ constexpr int WALK_MAX_LISTS = 4 * WALK_THREADS;              // Tq * nprobe
 constexpr int WALK_SHORT_ENTRIES = 4096;                      // short-list windows in all
 constexpr int WALK_BUCKET = WALK_SHORT_ENTRIES + WALK_MAX_LONG * 64;
 constexpr int WALK_DOC_BITS = 13;   // a bucket entry: list index << 13 | document in the range
+
+// Dense groups of a query up to which a range is walked through their table of
+// sums (see k_cand_walk), and the entries such a range holds at most.
+constexpr int WALK_TAB_BITS = 11;
+constexpr int WALK_NODES = 4096;
+constexpr int WALK_HITS = (WALK_BUCKET - WALK_NODES) / WALK_WAVES;  // documents with entries a wave lists at a time
 
 // Window of a thread's short list: WIN = 8, 4 or 2 entries as a thread owns
 // 1, 2 or 4 lists (WALK_SHORT_ENTRIES in all).
@@ -152,7 +177,8 @@ __device__ __forceinline__ void load_window(const int32_t *lp, int32_t pos, int3
 
 // Byte offsets of the walk's LDS arrays (each 16-byte aligned).
 struct WalkLds {
-  size_t smask, sfp, bucket, ll, lmask, lsum, skey, scid, dcount, bcnt, bbase, dgm, dgs, dls, nlong, total;
+  size_t smask, sfp, bucket, ll, lmask, lsum, skey, scid, dcount, bcnt, bbase, dgm, dgs, dls, nlong, dtab, dtok, dgrp,
+      total;
 };
 __host__ __device__ inline WalkLds walk_lds_layout(int R, int mask_bytes, int nprobe, int Tq) {
   const size_t nl = (size_t)nprobe * Tq;
@@ -170,20 +196,26 @@ __host__ __device__ inline WalkLds walk_lds_layout(int R, int mask_bytes, int np
   L.lmask = take(nl * mask_bytes);
   L.lsum = take(nl * 4);
   L.skey = take(nl * 4);
-  L.scid = take(nl * 4);
   L.dcount = take((size_t)nprobe * 4);
   L.bcnt = take((size_t)nprobe * 4);
   L.bbase = take((size_t)nprobe * 4);
+  // the table takes the place of what its ranges do not read, so that a query
+  // that had two workgroups a CU (640 to 928 lists: with 8 KB more, one) keeps them
+  L.dtab = o;
+  L.scid = take(nl * 4);
   L.dgm = take(nl * mask_bytes);
   L.dgs = take(nl * 4);
   L.dls = take(nl);
-  L.nlong = take(4);
+  o = o > L.dtab + (4u << WALK_TAB_BITS) ? o : L.dtab + (4u << WALK_TAB_BITS);
+  L.nlong = take(12);
+  L.dtok = take(64 * 2);
+  L.dgrp = take(WALK_TAB_BITS * 8);
   L.total = o;
   return L;
 }
 
 template <typename MaskT, int R, int LPT>
-__global__ __launch_bounds__(WALK_THREADS) void k_cand_walk(
+__global__ __launch_bounds__(WALK_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_cand_walk(
     const int32_t *__restrict__ cent_ids, const int32_t *__restrict__ cent_keys, int64_t nq, int Tq, int TQP,
     int nprobe, const int64_t *__restrict__ ivf_off, const int32_t *__restrict__ ivf_doc, int64_t ndocs, int ncent,
     int ndense, const int8_t *__restrict__ dense_slot, const uint64_t *__restrict__ doc_dense,
@@ -211,7 +243,10 @@ __global__ __launch_bounds__(WALK_THREADS) void k_cand_walk(
   MaskT *dgm = (MaskT *)(walk_lds + lay.dgm);            // [nl] token masks
   int32_t *dgs = (int32_t *)(walk_lds + lay.dgs);        // [nl] score sums
   int8_t *dls = (int8_t *)(walk_lds + lay.dls);          // [nl] dense slots
-  int32_t *nlong = (int32_t *)(walk_lds + lay.nlong);    // wave-owned lists
+  int32_t *nlong = (int32_t *)(walk_lds + lay.nlong);    // [3] wave-owned lists, dense groups, entries of the range
+  int32_t *dtab = (int32_t *)(walk_lds + lay.dtab);      // [2^g] F' of the dense groups alone, by their hits, on scid .. dls
+  uint16_t *dtok = (uint16_t *)(walk_lds + lay.dtok);    // [Tq] the dense groups that hold a token
+  int2 *dgrp = (int2 *)(walk_lds + lay.dgrp);            // [g] dense groups by rank: list index r * Tq + j, slot
   // workgroup b runs on XCD b % 8: with 8 or more queries, the groups of
   // query q run on XCD q % 8; fewer queries spread over every XCD
   const int b = blockIdx.x;
@@ -229,7 +264,7 @@ __global__ __launch_bounds__(WALK_THREADS) void k_cand_walk(
     skey[t] = cent_keys[e];
   }
   for (int r = threadIdx.x; r < nprobe; r += WALK_THREADS) dcount[r] = 0;
-  if (threadIdx.x == 0) *nlong = 0;
+  if (threadIdx.x < 3) nlong[threadIdx.x] = 0;
   __syncthreads();
   // classify list t = threadIdx.x + WALK_THREADS * i: group head or not,
   // dense, long or short; a short list stays with this thread (slot i)
@@ -266,6 +301,8 @@ __global__ __launch_bounds__(WALK_THREADS) void k_cand_walk(
       dls[r * Tq + k] = dense_slot[c];
       dgm[r * Tq + k] = gm;
       dgs[r * Tq + k] = gs;
+      const int d = atomicAdd(&nlong[1], 1);
+      if (d < WALK_TAB_BITS) ((int2 *)bucket)[d] = make_int2(t, dense_slot[c]);
       continue;
     }
     const int64_t beg = ivf_off[c], end = ivf_off[c + 1];
@@ -295,6 +332,50 @@ __global__ __launch_bounds__(WALK_THREADS) void k_cand_walk(
     load_window(S[i].lp, pos, len, S[i].e);
   }
   __syncthreads();
+  // the dense groups in rank order, the groups of each token, and the table:
+  // entry x is the sum of the best keys of the tokens that the groups of x hold
+  const int ng = nlong[1];
+  bool tab = ng <= WALK_TAB_BITS;  // uniform
+  if (tab) {
+    if ((int)threadIdx.x < ng) {
+      const int2 me = ((const int2 *)bucket)[threadIdx.x];
+      int at = 0;
+      for (int k = 0; k < ng; ++k) {
+        const int t = ((const int2 *)bucket)[k].x;
+        at += t < me.x ? 1 : 0;
+      }
+      dgrp[at] = me;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < Tq) {
+      int m = 0;
+      for (int k = 0; k < ng; ++k) m |= (int)((lmask[dgrp[k].x] >> threadIdx.x) & 1) << k;
+      dtok[threadIdx.x] = (uint16_t)m;
+    }
+    for (int x = threadIdx.x; x < (1 << ng); x += WALK_THREADS) {
+      MaskT seen = 0;
+      int32_t f = 0;
+      for (int k = 0; k < ng; ++k) {
+        if (!((x >> k) & 1)) continue;
+        const int t = dgrp[k].x;
+        const MaskT gm = lmask[t], fresh = gm & ~seen;
+        seen |= gm;
+        if (fresh == gm) {
+          f += lsum[t];
+        } else {
+          const int32_t *keys = skey + (t - __builtin_ctzll((unsigned long long)gm));
+          for (MaskT m = fresh; m; m &= m - 1) f += keys[__builtin_ctzll((unsigned long long)m)];
+        }
+      }
+      dtab[x] = f;
+    }
+    // the histogram of the group's ranges, and the documents' chains
+    for (int i = threadIdx.x; i < SEL_BINS; i += WALK_THREADS) ((uint32_t *)smask)[i] = 0;
+    for (int v = threadIdx.x; v < R; v += WALK_THREADS) sfp[v] = 0;
+    __syncthreads();
+  }
+  // lane k: the dense group k's slot
+  const int slots = tab && lane < ng ? dgrp[lane].y : 0;
   // the wave's lists and their windows: slot i is list wave + WALK_WAVES * i
   const int nlw = min(*nlong, WALK_MAX_LONG);
   // (lane l holds entry pos + l, loaded as is: lanes past the list's end hold
@@ -320,6 +401,239 @@ __global__ __launch_bounds__(WALK_THREADS) void k_cand_walk(
     const int64_t d0 = (int64_t)rg * R;
     const int64_t d1 = min(ndocs, d0 + R);
     const int nd = (int)(d1 - d0);
+    if (tab) {  // uniform
+      // ---- the range through chains of entries and the dense groups' table
+      uint32_t *hsh = (uint32_t *)smask;    // [SEL_BINS] the histogram of the group's ranges so far
+      uint32_t *chain = (uint32_t *)sfp;    // [R] 1 + a document's last entry, 0: none
+      int32_t *nent = nlong + 2;
+      // every list's entries in the range: list index << 16 | 1 + the document's entry before
+      auto link = [&](int node, int t, int v) {
+        if (node < WALK_NODES) bucket[node] = (uint32_t)t << 16 | atomicExch(&chain[v], (uint32_t)node + 1);
+      };
+      int snew[LPT];
+      int32_t spos[LPT];
+#pragma unroll
+      for (int i = 0; i < LPT; ++i) {
+        int mt = 0;
+#pragma unroll
+        for (int u = 0; u < WIN; ++u) mt += (u < S[i].avail && S[i].e[u] < d1) ? 1 : 0;
+        snew[i] = mt;
+        spos[i] = S[i].pos0 + mt;
+        const uint32_t incl = wave_incl_scan((uint32_t)mt);
+        const int all = __builtin_amdgcn_readlane((int)incl, 63);
+        if (all == 0) continue;  // wave-uniform
+        int base = 0;
+        if (lane == 0) base = atomicAdd(nent, all);
+        base = __builtin_amdgcn_readfirstlane(base) + (int)incl - mt;
+        // (the exchanges are issued together, their results used afterwards)
+        uint32_t before[WIN];
+#pragma unroll
+        for (int u = 0; u < WIN; ++u) {
+          before[u] = 0;
+          if (u < mt && base + u < WALK_NODES)
+            before[u] = atomicExch(&chain[(int)(S[i].e[u] - d0)], (uint32_t)(base + u) + 1);
+        }
+#pragma unroll
+        for (int u = 0; u < WIN; ++u)
+          if (u < mt && base + u < WALK_NODES) bucket[base + u] = (uint32_t)S[i].t << 16 | before[u];
+        // a list with more entries in the range than its window goes on through memory
+        if (mt == S[i].avail && mt > 0) {
+          while (spos[i] < S[i].len) {
+            const int32_t dd = S[i].lp[spos[i]];
+            if (dd >= d1) break;
+            link(atomicAdd(nent, 1), S[i].t, (int)(dd - d0));
+            ++spos[i];
+          }
+        }
+      }
+      int lnew[WALK_LONG_SLOTS];  // wave-uniform
+#pragma unroll
+      for (int i = 0; i < WALK_LONG_SLOTS; ++i) {
+        lnew[i] = 0;
+        const int k = wave + WALK_WAVES * i;
+        if (k >= nlw) continue;  // wave-uniform
+        const LongList w = LL[k];
+        int32_t doc = w.pos + lane < w.len ? lw[i] : INT32_MAX;
+        for (;;) {
+          const bool in = doc < d1;
+          const unsigned long long ins = __ballot(in);  // a prefix of the lanes: the list ascends
+          const int n = __popcll(ins);
+          if (n > 0) {
+            int base = 0;
+            if (lane == 0) base = atomicAdd(nent, n);
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (in) link(base + lane, w.t, (int)(doc - d0));
+          }
+          lnew[i] += n;
+          if (n < 64) break;
+          const int32_t p = w.pos + lnew[i] + lane;
+          doc = p < w.len ? ivf_doc[w.beg + p] : INT32_MAX;
+        }
+      }
+      __syncthreads();  // the chains are complete
+      if (*nent <= WALK_NODES) {  // uniform
+        // each wave takes the documents its threads own, four of a thread at a
+        // time: without entries F' is the table's; the others are listed and
+        // taken one a lane
+        uint32_t *hl = bucket + WALK_NODES + wave * WALK_HITS;
+        constexpr int HALF = DPT < 4 ? DPT : 4;
+        static_assert(HALF * 64 <= WALK_HITS, "a wave lists every document of a step");
+#pragma unroll
+        for (int i0 = 0; i0 < DPT; i0 += HALF) {
+          int32_t x[HALF];
+          bool hit[HALF];
+          int nh = 0;  // wave-uniform
+          uint32_t bits[HALF];
+#pragma unroll
+          for (int i = 0; i < HALF; ++i) bits[i] = 0;
+          for (int k = 0; k < ng; ++k) {
+            const int sl = __builtin_amdgcn_readlane(slots, k);
+#pragma unroll
+            for (int i = 0; i < HALF; ++i) {
+              const uint32_t w = sl < 32 ? (uint32_t)dm[i0 + i] : (uint32_t)(dm[i0 + i] >> 32);
+              bits[i] |= ((w >> (sl & 31)) & 1u) << k;
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < HALF; ++i) {
+            const int v = threadIdx.x + WALK_THREADS * (i0 + i);
+            const int idx = (int)bits[i];
+            hit[i] = chain[v] != 0;
+            x[i] = idx ? dtab[idx] : NO_HIT;
+            const unsigned long long hs = __ballot(hit[i]);
+            if (hit[i]) hl[nh + __popcll(hs & ((1ull << lane) - 1))] = (uint32_t)v << 16 | (uint32_t)idx;
+            nh += __popcll(hs);
+          }
+          for (int b0 = 0; b0 < nh; b0 += 64) {
+            const bool on = b0 + lane < nh;
+            const uint32_t h = on ? hl[b0 + lane] : 0;
+            const int v = (int)(h >> 16), idx = (int)(h & 0xFFFFu);
+            // the document's entries in rank order (list indexes ascend with the rank)
+            uint32_t a[4] = {0xFFFFu, 0xFFFFu, 0xFFFFu, 0xFFFFu};
+            uint32_t e = on ? chain[v] : 0;
+            int n = 0;
+            while (e && n <= 4) {
+              const uint32_t y = bucket[e - 1];
+              uint32_t t = y >> 16;
+#pragma unroll
+              for (int u = 0; u < 4; ++u) {
+                const uint32_t lo = min(a[u], t);
+                t = max(a[u], t);
+                a[u] = lo;
+              }
+              e = y & 0xFFFFu;
+              ++n;
+            }
+            if (on && n <= 4) {
+              // the tokens of an entry's group that no better entry has credited
+              // take its key where no dense group of a better rank holds them,
+              // in place of a worse one's
+              int32_t f = dtab[idx];
+              MaskT seen = 0;
+#pragma unroll
+              for (int u = 0; u < 4; ++u) {
+                if (a[u] == 0xFFFFu) continue;
+                const MaskT gm = lmask[a[u]];
+                const int rb = (int)a[u] - __builtin_ctzll((unsigned long long)gm);  // r * Tq: the head is the first token
+                for (MaskT m = gm & ~seen; m; m &= m - 1) {
+                  const int j = __builtin_ctzll((unsigned long long)m);
+                  const int dk = idx & dtok[j];
+                  if (dk) {
+                    const int td = dgrp[__builtin_ctz(dk)].x;
+                    const int db = td - __builtin_ctzll((unsigned long long)lmask[td]);
+                    if (db > rb) f += skey[rb + j] - skey[db + j];
+                  } else {
+                    f += skey[rb + j];
+                  }
+                }
+                seen |= gm;
+              }
+              chain[v] = (uint32_t)f;
+            }
+            // a document with more entries: the wave takes it, a token a lane,
+            // each the largest of its keys
+            for (unsigned long long big = __ballot(on && n > 4); big; big &= big - 1) {
+              const int l = __builtin_ctzll(big);
+              const int bv = __builtin_amdgcn_readlane(v, l), bidx = __builtin_amdgcn_readlane(idx, l);
+              int32_t best = INT_MIN;
+              auto take = [&](int t) {
+                const MaskT gm = lmask[t];
+                if (lane < Tq && ((gm >> lane) & 1)) best = max(best, skey[t - __builtin_ctzll((unsigned long long)gm) + lane]);
+              };
+              uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)chain[bv]);
+              while (c) {
+                const uint32_t y = (uint32_t)__builtin_amdgcn_readfirstlane((int)bucket[c - 1]);
+                take((int)(y >> 16));
+                c = y & 0xFFFFu;
+              }
+              for (int k = 0; k < ng; ++k)
+                if ((bidx >> k) & 1) take(dgrp[k].x);
+              const uint32_t sum = wave_incl_scan(best == INT_MIN ? 0u : (uint32_t)best);
+              if (lane == 63) chain[bv] = sum;
+            }
+          }
+          int32_t *f = fp + q * ndocs + d0;
+#pragma unroll
+          for (int i = 0; i < HALF; ++i) {
+            const int v = threadIdx.x + WALK_THREADS * (i0 + i);
+            if (hit[i]) {
+              x[i] = (int32_t)chain[v];
+              chain[v] = 0;
+            }
+            if (v < nd) {
+              if (deleted && ((deleted[(d0 + v) >> 6] >> ((d0 + v) & 63)) & 1)) x[i] = NO_HIT;
+              f[v] = x[i];
+              if (x[i] != NO_HIT) atomicAdd(&hsh[fp_key(x[i]) >> 20], 1u);
+            }
+          }
+        }
+        // the next range's inputs
+#pragma unroll
+        for (int i = 0; i < LPT; ++i) {
+          S[i].pos0 = spos[i];
+          S[i].avail = S[i].rank < 0 ? 0 : min(WIN, S[i].len - S[i].pos0);
+          load_window(S[i].lp, S[i].pos0, S[i].len, S[i].e);
+        }
+#pragma unroll
+        for (int i = 0; i < WALK_LONG_SLOTS; ++i) {
+          const int k = wave + WALK_WAVES * i;
+          if (k < nlw) {  // wave-uniform
+            const LongList w = LL[k];
+            const int32_t pos = w.pos + lnew[i];
+            lw[i] = ivf_doc[w.beg + min(pos + lane, w.len - 1)];
+            if (lane == 0) LL[k].pos = pos;
+          }
+        }
+        if (rg + 1 < rg1) {
+#pragma unroll
+          for (int i = 0; i < DPT; ++i) {
+            const int64_t v = d1 + threadIdx.x + WALK_THREADS * i;
+            dm[i] = ndense > 0 && v < ndocs ? doc_dense[v] : 0;
+          }
+        }
+        __syncthreads();  // the range has been read
+        if (threadIdx.x == 0) *nent = 0;
+        __syncthreads();
+        continue;
+      }
+      // more entries than the chains hold: the histogram so far goes out, and
+      // the range (and the group's others) are walked rank by rank, with the
+      // dense groups' arrays back in the table's place
+      uint32_t *hq = hist + q * SEL_BINS;
+      for (int i = threadIdx.x; i < SEL_BINS; i += WALK_THREADS)
+        if (hsh[i]) atomicAdd(&hq[i], hsh[i]);
+      if ((int)threadIdx.x < ng) {
+        const int2 me = dgrp[threadIdx.x];
+        const int r = me.x / Tq;
+        int k = 0;
+        for (int b = 0; b < (int)threadIdx.x; ++b) k += dgrp[b].x / Tq == r ? 1 : 0;
+        dls[r * Tq + k] = (int8_t)me.y;
+        dgm[r * Tq + k] = lmask[me.x];
+        dgs[r * Tq + k] = lsum[me.x];
+      }
+      tab = false;
+      __syncthreads();
+    }
     for (int v = threadIdx.x; v < R; v += WALK_THREADS) {
       smask[v] = 0;
       sfp[v] = 0;
@@ -504,6 +818,12 @@ __global__ __launch_bounds__(WALK_THREADS) void k_cand_walk(
     for (int i = threadIdx.x; i < SEL_BINS; i += WALK_THREADS)
       if (sh[i]) atomicAdd(&hq[i], sh[i]);
     __syncthreads();  // sh (the mask array) is cleared by the next range
+  }
+  if (tab) {
+    uint32_t *hq = hist + q * SEL_BINS;
+    const uint32_t *hsh = (const uint32_t *)smask;
+    for (int i = threadIdx.x; i < SEL_BINS; i += WALK_THREADS)
+      if (hsh[i]) atomicAdd(&hq[i], hsh[i]);
   }
 }
 
@@ -1379,13 +1699,16 @@ static int keep_chunks(int64_t nq, int64_t ndocs) {
   return P <= SEL_MAX_CHUNKS && nq * P <= 16384 ? (int)P : 0;
 }
 
+// At least the split select's size whichever is used, so that what fits a
+// fixed scratch does not depend on the choice.
 size_t select_scratch_bytes(int64_t nq, int64_t ndocs, int ncand) {
-  if (const int64_t K = keep_chunks(nq, ndocs))
-    return (size_t)nq * (sizeof(SelState) + (size_t)K * (24 + 8) + (size_t)keep_cap(ndocs, ncand) * 8) + 1024;
   const int P = select_chunks(nq, ndocs);
   const size_t cap = (size_t)sel_list_cap(ndocs, P, ncand);
-  return (size_t)nq * (sizeof(SelState) + (SEL_BINS + 256) * 4 + (size_t)P * (24 + 256 * 4 + 4 + 4 + cap * 8)) +
-         (size_t)nq * P * (4 + cap * 8) + 1024;
+  const size_t split = (size_t)nq * (sizeof(SelState) + (SEL_BINS + 256) * 4 +
+                                     (size_t)P * (24 + 256 * 4 + 4 + 4 + cap * 8)) + (size_t)nq * P * (4 + cap * 8) + 1024;
+  const int64_t K = keep_chunks(nq, ndocs);
+  const size_t keep = (size_t)nq * (sizeof(SelState) + (size_t)K * (24 + 8) + (size_t)keep_cap(ndocs, ncand) * 8) + 1024;
+  return K ? std::max(split, keep) : split;
 }
 
 void launch_select(const int32_t *fp, const uint32_t *hist, uint32_t *nlist, int64_t nq, int64_t ndocs, int ncand,

@@ -1,0 +1,106 @@
+"""The candidate walk of an index with dense lists against the oracle: ranges
+through chains of entries and the dense groups' table, ranges with more
+entries than the chains hold (walked rank by rank), queries with more dense
+groups than the table takes, documents with more entries than a lane sorts,
+query tokens that share centroids, both token-mask widths and deletions."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from util_gpu import check_search, q_tensor, say, setup
+
+pytestmark = pytest.mark.gpu
+
+
+def _check_prune(idx, ref, q, nprobe, ncand, label):
+    say("prune", label)
+    cand, keys, nval = (x.cpu().numpy() for x in idx.prune(q_tensor(q, "bf16"), nprobe, ncand))
+    for i in range(len(q)):
+        n = ref["n_cand"][i]
+        order = np.argsort(ref["cand"][i, :n])
+        assert nval[i] == n, (label, i)
+        assert np.array_equal(cand[i, :n], ref["cand"][i, :n][order]), (label, i)
+        assert np.array_equal(keys[i, :n], ref["cand_keys"][i, :n][order]), (label, i)
+
+
+@pytest.mark.parametrize("ndocs,ncent,nprobe,Tq", [
+    (4096, 16_384, 12, 32),  # few entries, one whole range
+    (9001, 8192, 16, 32),    # 512 lists, a ragged last range
+    (9001, 8192, 40, 32),    # windows of two entries, many dense groups
+    (12_289, 600, 9, 32),    # more entries in a range than the chains hold
+    (5000, 4096, 12, 64),    # 64-bit masks, ranges of 2048
+    (6145, 700, 30, 64),     # 64-bit masks and a full walk rank by rank
+    (4097, 2048, 1, 5),      # one rank, few tokens
+    (9001, 8192, 4, 32),     # few ranks
+])
+def test_prune(ndocs, ncent, nprobe, Tq):
+    w, c, _, cl, oi, idx = setup("1m", ndocs=ndocs, ncent=ncent)
+    q, _ = c.queries(5, Tq, query_seed=ncent + nprobe)
+    q[4] = np.repeat(q[4, :(Tq + 3) // 4], 4, axis=0)[:Tq]  # tokens four times over
+    ncand = ndocs  # every hit with its F'
+    _check_prune(idx, oi.prune(q, nprobe, ncand), q, nprobe, ncand, f"{ndocs} docs, {ncent} cents, np {nprobe}, Tq {Tq}")
+    check_search(idx, oi, q, nprobe, 300, 20, "bf16", "search")
+
+
+def test_group_counts_on_both_sides_of_the_table():
+    """Queries of the cases above fall on both sides of the 11 groups that the
+    table takes: with nprobe 1 to 40 their dense groups run from none to many."""
+    w, c, _, cl, oi, idx = setup("1m", ndocs=9001, ncent=8192)
+    docs = np.repeat(np.arange(9001), c.lengths)
+    in_list = np.zeros(8192, np.int64)
+    np.add.at(in_list, np.unique(np.stack([cl, docs]), axis=1)[0], 1)
+    dense = set(np.argsort(-in_list, kind="stable")[:64]) & set(np.nonzero(in_list * 16 > 9001)[0])
+    q, _ = c.queries(24, 32, query_seed=77)
+    groups = []
+    for qq in q:
+        ids = np.asarray(oracle.probe(oracle.centroid_scores(qq, c.centroids_k), 16)[0])
+        groups.append(sum(len(dense & set(ids[:, r])) for r in range(16)))
+    assert min(groups) <= 11 < max(groups), groups
+    _check_prune(idx, oi.prune(q, 16, 9001), q, 16, 9001, f"groups {min(groups)}..{max(groups)}")
+
+
+def test_deleted_documents():
+    w, c, _, _, oi, _ = setup("1m", ndocs=9001, ncent=8192)
+    from util_build import product_builder
+    idx = product_builder(c, w.nbits).upload(0)
+    gone = np.random.default_rng(3).choice(9001, 1500, replace=False)
+    idx.delete(gone)
+    q, _ = c.queries(4, 32, query_seed=9)
+    ids, _ = idx.search(q_tensor(q, "bf16"), 16, 400, 30)
+    torch.cuda.synchronize()
+    deleted = np.zeros(9001, bool)
+    deleted[gone] = True
+    ref = oracle.search_deleted(oi, q, 16, 400, 30, deleted)
+    assert np.array_equal(ids.cpu().numpy(), ref["ids"])
+
+
+@pytest.mark.parametrize("row,nprobe", [(42, 11), (70, 12)])
+def test_chains_overflow_in_a_workgroups_second_range(row, nprobe):
+    """A workgroup of two ranges whose second holds more entries than the
+    chains: its histogram and its lists go on rank by rank.  17,000 queries
+    make the walk's workgroups take two of the four ranges each."""
+    w, c, _, cl, oi, idx = setup("1m", ndocs=16_384, ncent=16_384)
+    q, _ = c.queries(120, 32, query_seed=5)
+    pairs = np.unique(np.stack([cl, np.repeat(np.arange(16_384), c.lengths)]), axis=1)
+    count = np.zeros((16_384, 4), np.int64)
+    np.add.at(count, (pairs[0], pairs[1] // 4096), 1)
+    total = count.sum(1)
+    dense = np.nonzero((total * 16 > 16_384) & (np.argsort(np.argsort(-total, kind="stable")) < 64))[0]
+    ids = np.asarray(oracle.probe(oracle.centroid_scores(q[row], c.centroids_k), nprobe)[0])
+    ranks = [np.setdiff1d(ids[:, r], dense) for r in range(nprobe)]
+    entries = sum(count[x].sum(0) for x in ranks)
+    assert sum(len(np.intersect1d(ids[:, r], dense)) for r in range(nprobe)) <= 11
+    assert any(entries[a] <= 4096 < entries[a + 1] for a in (0, 2)), entries
+    few = q[[row, 0, 1, 2, 3]]
+    say("prune 17,000 queries", row, nprobe)
+    many = q_tensor(few, "bf16").repeat(3400, 1, 1)
+    cand, keys, nval = idx.prune(many, nprobe, 500)
+    cand, keys, nval = (x.view(3400, 5, *x.shape[1:]) for x in (cand, keys, nval))
+    ref = oi.prune(few, nprobe, 500)
+    for i in range(5):
+        assert ref["n_cand"][i] == 500 and bool((nval[:, i] == 500).all())
+        order = np.argsort(ref["cand"][i, :500])
+        assert np.array_equal(cand[0, i].cpu().numpy(), ref["cand"][i, :500][order]), i
+        assert np.array_equal(keys[0, i].cpu().numpy(), ref["cand_keys"][i, :500][order]), i
+        assert bool((cand[:, i] == cand[0, i]).all()) and bool((keys[:, i] == keys[0, i]).all()), i
