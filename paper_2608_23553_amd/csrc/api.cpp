@@ -283,8 +283,9 @@ static int ensure_scratch(chimera_index *idx, size_t bytes) {
 static size_t scratch_budget() {
   const char *s = std::getenv("CHIMERA_SCRATCH_MB");
   // larger sub-batches amortise each launch's tail: at 8.8M documents a
-  // query needs about 72 MB, and a 4096-query batch takes 6,862 QPS in 9
-  // sub-batches (32 GiB), 6,898 in 5 (64 GiB) and 6,990 in 3 (128 GiB);
+  // query that the scorer takes by itself needs about 72 MB, and a 4096-query
+  // batch took 6,862 QPS in 9 sub-batches (32 GiB), 6,898 in 5 (64 GiB) and
+  // 6,990 in 3 (128 GiB); a batch scored by document needs 36 MB a query;
   // the arena is sized to the batch, so small batches take little of it
   size_t mb = s ? (size_t)std::strtoull(s, nullptr, 10) : 131072;
   if (mb < 16) mb = 16;
@@ -381,6 +382,7 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
     // the sub-batches until their scratch fits, down to one query
     while (rc == CHIMERA_E_NOMEM && B > 1) {
       B = (B + 1) / 2;
+      if (by_doc && !doc_score_grouped(B, idx->ndocs, idx->ntok, idx->ndense, ncand)) by_doc = false;
       need = need_for(B);
       rc = ensure_scratch(idx, need);
     }
