@@ -242,7 +242,7 @@ static size_t carve_bytes(const chimera_index *idx, int64_t nb, int TQP, int npr
   if (rq && !by_doc) b += align_up((size_t)rows * RQ_ROW_BYTES) + align_up((size_t)rows * 4);  // query limbs, qsum
   if (stop >= STOP_CANDIDATES) {
     b += align_up((size_t)nb * idx->ndocs * 4);  // F'
-    b += align_up((size_t)nb * 4097 * 4);        // select histogram and list length
+    b += align_up((size_t)nb * 4096 * 4);        // select histogram
   }
   if (stop == STOP_CANDIDATES) b += align_up((size_t)(nb + 1) * 8);  // counts
   if (stop >= STOP_PRUNE)  // cand, keys, F^, n, select state
@@ -436,10 +436,14 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
       continue;
     }
     int32_t *fp = cv.take<int32_t>((size_t)nb * idx->ndocs);
-    uint32_t *hist = cv.take<uint32_t>((size_t)nb * 4097);  // and the select's list lengths [nb]
+    uint32_t *hist = cv.take<uint32_t>((size_t)nb * 4096);
+    // the select's scratch follows the histogram, so that one fill clears what
+    // has to be zero of both
+    char *selw = stop >= STOP_PRUNE ? cv.take<char>(select_scratch_bytes(nb, idx->ndocs, ncand)) : nullptr;
     if (cv.off > scratch_cap) return fail(CHIMERA_E_NOMEM, "internal: scratch plan overflow");
     stage_mark(idx, s, mark);
-    launch_fill_zero(hist, (size_t)nb * 4097 * 4, s);
+    static_assert(4096 * 4 % 256 == 0, "no gap after the histogram");
+    launch_fill_zero(hist, (size_t)nb * 4096 * 4 + (selw ? select_zero_bytes(nb, idx->ndocs) : 0), s);
     if (refine == CHIMERA_REFINE_TOKEN)
       launch_refine_walk(ci, ck, Qs, nb, Tq, TQP, nprobe, idx->d_tok_off, idx->d_ivf_tok, idx->d_tok_doc,
                          idx->d_doc_off, idx->d_codes, idx->nbits, idx->h_weights, idx->ndocs,
@@ -475,9 +479,7 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
     int32_t *fhat = stop >= STOP_FULL ? cv.take<int32_t>((size_t)nb * ncand) : nullptr;
     if (cv.off > scratch_cap) return fail(CHIMERA_E_NOMEM, "internal: scratch plan overflow");
     stage_mark(idx, s, mark);
-    char *selw = cv.take<char>(select_scratch_bytes(nb, idx->ndocs, ncand));
-    if (cv.off > scratch_cap) return fail(CHIMERA_E_NOMEM, "internal: scratch plan overflow");
-    launch_select(fp, hist, hist + nb * 4096, nb, idx->ndocs, ncand, selw, cand, candk, nval, s);
+    launch_select(fp, hist, nb, idx->ndocs, ncand, selw, cand, candk, nval, s);
     CHIMERA_HIP(hipGetLastError());
     if (stop == STOP_PRUNE) continue;
     // RaBitQ scoring: the rotated queries as int8 limbs

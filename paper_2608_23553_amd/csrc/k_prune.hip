@@ -1429,37 +1429,76 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_sel_scan(int P, int ncand, Se
 //               (every workgroup finds it for itself), and the chunk's
 //               documents whose top 12 bits reach it, in document order, at a
 //               place of the query's list reserved by one atomic;
-//  k_keep_cut   per query: T and the ties to keep from the list (bits 19..8,
-//               then 7..0), each chunk's kept and tied counts, their prefix
-//               sums, the number of candidates and the padding;
+//  k_keep_cut   T and the ties to keep (bits 19..8, then 7..0), each chunk's
+//               kept and tied counts, their prefix sums, the number of
+//               candidates and the padding;
 //  k_sel_write  per chunk, as in the split select.
-// A list that is full (counted past cap) is not used: k_keep_cut and
-// k_sel_write then read the query's F'.
+// How long a query's list gets is up to the data: the bins of the first pass
+// are 0.25 wide in F', so that few query tokens, or many ties, put most
+// documents into the bin that is cut.  A list of at most keep_short entries
+// is cut by one workgroup, from registers.  For a longer one every pass stays
+// spread over the chunks: k_keep_list adds the histogram of bits 19..8,
+// k_keep_cut has a workgroup for every four chunks, which record their counts
+// and the histogram of bits 7..0, and the one that arrives last finds T and
+// sums the chunks' counts.  (Lists of more than cap entries are not kept: F'
+// is read instead.)
 // One query of 100,000 documents: 54 us in seven launches before, now 22 us;
 // of 2.2M documents 116 us, now 45 us; 16 queries of 1,000 documents 60 us,
 // now 17 us (the list in registers and the prefix sums by DPP are half of
-// that: 35, 61 and 31 us without them).
+// that: 35, 61 and 31 us without them).  Long lists, 1M documents: one query of
+// four tokens 58 us (1,600 us when one workgroup read F' three times, 76 us in
+// seven launches), 16 of them 136 us (1,660 and 138), 64 of them 385 us (2,750
+// and 325); one query of 262,144 candidates 48 us (311 and 68).
 constexpr int SEL_CHUNK = 4096;
 constexpr int SEL_MAX_CHUNKS = 3072;  // of a query: their counts are in LDS, 57 KB with the bins
 
-__host__ __device__ inline int64_t keep_cap(int64_t ndocs, int ncand) {
-  return std::min<int64_t>(ndocs, 4 * (int64_t)ncand + 4096);
+// Entries of the list a thread of k_keep_cut keeps in registers over the passes.
+constexpr int KEEP_REGS = 24;
+constexpr int CUT_CHUNKS = SEL_THREADS / SPLIT_THREADS;  // of a workgroup of k_keep_cut
+
+// Entries that the list of a query in K chunks holds: as many as both of the
+// split select's lists, in whose scratch it is.
+__host__ inline int64_t keep_cap(int64_t ndocs, int64_t K, int ncand) {
+  return std::min<int64_t>(ndocs, 2 * K * sel_list_cap(ndocs, (int)K, ncand));
+}
+// Entries up to which one workgroup cuts a list.
+__host__ __device__ inline uint32_t keep_short(int64_t cap) {
+  return (uint32_t)std::min<int64_t>(cap, KEEP_REGS * SEL_THREADS);
 }
 
-__global__ __launch_bounds__(SPLIT_THREADS) void k_keep_list(const int32_t *__restrict__ fp,
-                                                             const uint32_t *__restrict__ hist1, int64_t ndocs, int P,
-                                                             int ncand, int64_t cap, int2 *__restrict__ list,
-                                                             uint32_t *__restrict__ nlist, uint2 *__restrict__ part) {
-  constexpr int W = SPLIT_THREADS / 64;
-  __shared__ uint32_t wsum[2][W];
-  __shared__ uint2 s_bin;
-  __shared__ uint32_t s_at;
-  const int64_t q = blockIdx.x / P;
-  const int c = blockIdx.x % P;
-  const int64_t v0 = (int64_t)c * SEL_CHUNK + threadIdx.x * 16, v1 = min(ndocs, (int64_t)(c + 1) * SEL_CHUNK);
-  const int32_t *f = fp + q * ndocs;
-  int32_t x[16];
-  if (((uintptr_t)f & 15) == 0 && v0 + 16 <= v1) {
+// Scratch of the small batch's select, in this order: the arrays that are zero
+// on entry (select_zero_bytes), then the others.
+struct SmallSel {
+  uint32_t *hist2, *hist3;     // [nq][4096], [nq][256] bits 19..8 and 7..0 of long lists
+  uint32_t *nlist, *arrived;   // [nq] list lengths; [nq] workgroups of k_keep_cut that are done
+  SelState *st;                // [nq]
+  long long *counts;           // [nq][K][3]
+  uint2 *part;                 // [nq][K] where a chunk's entries start in the list, and how many they are
+  uint32_t *rec;               // [nq][K][2] a chunk's documents above the 24-bit prefix, and in it
+  uint32_t *rows;              // [nq][K][128] a chunk's histogram of bits 7..0, two counts a word
+  int2 *list;                  // [nq][cap] document, F'
+};
+__host__ inline SmallSel small_sel(void *scratch, int64_t nq, int64_t K) {
+  SmallSel x;
+  x.hist2 = (uint32_t *)scratch;
+  x.hist3 = x.hist2 + nq * SEL_BINS;
+  x.nlist = x.hist3 + nq * 256;
+  x.arrived = x.nlist + nq;
+  x.st = (SelState *)(x.arrived + nq);
+  x.counts = (long long *)(x.st + nq);
+  x.part = (uint2 *)(x.counts + 3 * nq * K);
+  x.rec = (uint32_t *)(x.part + nq * K);
+  x.rows = x.rec + 2 * nq * K;
+  x.list = (int2 *)(x.rows + 128 * nq * K);
+  return x;
+}
+static size_t small_sel_bytes(int64_t nq, int64_t K, int64_t cap) {
+  return (size_t)((char *)(small_sel(nullptr, nq, K).list + nq * cap) - (char *)nullptr);
+}
+
+// F' of documents v0 .. v0 + 15 (those below v1; NO_HIT past it).
+__device__ __forceinline__ void load_fp16(const int32_t *f, int64_t v0, int64_t v1, int32_t (&x)[16]) {
+  if (((uintptr_t)f & 15) == 0 && v0 + 16 <= v1) {  // (v0 is a multiple of 16)
 #pragma unroll
     for (int i = 0; i < 16; i += 4) {
       const int4 y = *(const int4 *)(f + v0 + i);
@@ -1472,133 +1511,268 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_keep_list(const int32_t *__re
 #pragma unroll
     for (int i = 0; i < 16; ++i) x[i] = v0 + i < v1 ? f[v0 + i] : NO_HIT;
   }
+}
+
+__global__ __launch_bounds__(SPLIT_THREADS) void k_keep_list(const int32_t *__restrict__ fp,
+                                                             const uint32_t *__restrict__ hist1, int64_t ndocs, int P,
+                                                             int ncand, int64_t cap, SmallSel S) {
+  constexpr int W = SPLIT_THREADS / 64;
+  __shared__ uint32_t wsum[2][W];
+  __shared__ uint2 s_bin;
+  __shared__ uint32_t s_at;
+  __shared__ uint32_t h[SEL_BINS];
+  const int64_t q = blockIdx.x / P;
+  const int c = blockIdx.x % P;
+  const int64_t v0 = (int64_t)c * SEL_CHUNK + threadIdx.x * 16, v1 = min(ndocs, (int64_t)(c + 1) * SEL_CHUNK);
+  int32_t x[16];
+  load_fp16(fp + q * ndocs, v0, v1, x);
   const uint32_t nhit = find_bin<W, SEL_BINS / SPLIT_THREADS>(hist1 + q * SEL_BINS, (uint32_t)ncand, wsum[0], &s_bin);
-  const uint32_t b1 = nhit <= (uint32_t)ncand ? 0 : s_bin.x;  // no more hits than candidates: all are listed
+  const bool all = nhit <= (uint32_t)ncand;  // no more hits than candidates: all are listed
+  const uint32_t b1 = all ? 0 : s_bin.x;
+  // the whole list's length
+  const uint32_t nl = all ? nhit : s_bin.y + hist1[q * SEL_BINS + b1];
   uint32_t n = 0;
 #pragma unroll
   for (int i = 0; i < 16; ++i) n += x[i] != NO_HIT && (fp_key(x[i]) >> 20) >= b1;
   uint32_t tot;
   uint32_t pos = block_scan<W>(n, wsum[1], tot);
   if (threadIdx.x == 0) {
-    s_at = tot ? atomicAdd(&nlist[q], tot) : 0;
-    part[q * P + c] = make_uint2(s_at, tot);
+    s_at = tot ? atomicAdd(&S.nlist[q], tot) : 0;
+    S.part[q * P + c] = make_uint2(s_at, tot);
   }
+  const bool hist = nl > keep_short(cap) && !all && tot > 0;  // uniform
+  if (hist)
+    for (int i = threadIdx.x; i < SEL_BINS; i += SPLIT_THREADS) h[i] = 0;
   __syncthreads();
-  pos += s_at;
-  int2 *L = list + q * cap;
+  if (nl <= (uint64_t)cap) {  // uniform
+    pos += s_at;
+    int2 *L = S.list + q * cap;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (x[i] != NO_HIT && (fp_key(x[i]) >> 20) >= b1) {
+        if (pos < (uint64_t)cap) L[pos] = make_int2((int)(v0 + i), x[i]);
+        ++pos;
+      }
+  }
+  if (!hist) return;
 #pragma unroll
   for (int i = 0; i < 16; ++i)
-    if (x[i] != NO_HIT && (fp_key(x[i]) >> 20) >= b1) {
-      if (pos < (uint64_t)cap) L[pos] = make_int2((int)(v0 + i), x[i]);
-      ++pos;
-    }
+    if (x[i] != NO_HIT && (fp_key(x[i]) >> 20) == b1) atomicAdd(&h[(fp_key(x[i]) >> 8) & 4095u], 1u);
+  __syncthreads();
+  for (int i = threadIdx.x; i < SEL_BINS; i += SPLIT_THREADS)
+    if (h[i]) atomicAdd(&S.hist2[q * SEL_BINS + i], h[i]);
 }
 
-// Entries of the list a thread keeps in registers over the passes.
-constexpr int KEEP_REGS = 24;
+// Words that one workgroup writes and another of the same launch reads: agent
+// scope goes past the XCDs' caches, so the writer needs no write-back of its
+// whole L2 (a __threadfence in every wave cost 25 ns each: 0.9 of 1.3 ms for 64
+// queries of 1M documents), only its own stores to be done (wait_stores).
+__device__ __forceinline__ uint32_t load_agent(const uint32_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void store_agent(uint32_t *p, uint32_t x) {
+  __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void wait_stores() {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0);  // every counter at zero: stores and atomics are done
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
 
+// Workgroup b < nq: query b's list, when it is short.  Workgroup nq + q PB + g:
+// chunks CUT_CHUNKS g .. of query q (256 threads each), when its list is long.
 __global__ __launch_bounds__(SEL_THREADS) void k_keep_cut(const int32_t *__restrict__ fp,
-                                                          const uint32_t *__restrict__ hist1, int64_t ndocs, int P,
-                                                          int ncand, int64_t cap, const int2 *__restrict__ list,
-                                                          const uint32_t *__restrict__ nlist,
-                                                          SelState *__restrict__ st, long long *__restrict__ counts,
-                                                          int32_t *__restrict__ out_ids, int32_t *__restrict__ out_keys,
+                                                          const uint32_t *__restrict__ hist1, int64_t nq,
+                                                          int64_t ndocs, int P, int PB, int ncand, int64_t cap,
+                                                          SmallSel S, int32_t *__restrict__ out_ids,
+                                                          int32_t *__restrict__ out_keys,
                                                           int32_t *__restrict__ n_valid) {
   constexpr int W = SEL_THREADS / 64, PER = SEL_BINS / SEL_THREADS;
   __shared__ __align__(16) uint32_t hist[2][SEL_BINS];
   __shared__ uint32_t wsum[5][W];
   __shared__ uint2 s_bin[3];
+  __shared__ uint32_t s_cnt[CUT_CHUNKS][2], s_done;
   extern __shared__ uint32_t chunk_n[];  // [P] kept, [P] tied
-  const int64_t q = blockIdx.x;
-  const int64_t nl = nlist[q];
-  const bool from_list = nl <= cap;  // uniform
-  const int64_t n = from_list ? nl : ndocs;
-  const bool in_regs = from_list && n <= KEEP_REGS * SEL_THREADS;  // uniform
-  const int2 *L = list + q * cap;
-  const int32_t *f = fp + q * ndocs;
+  const bool one = (int64_t)blockIdx.x < nq;  // the whole list by this workgroup
+  const int64_t b = (int64_t)blockIdx.x - nq, q = one ? blockIdx.x : b / PB;
+  const uint32_t nl = S.nlist[q];
+  if (one != (nl <= keep_short(cap))) return;  // uniform
   int2 r[KEEP_REGS];
-  if (in_regs) {
+  if (one) {
+    const int2 *L = S.list + q * cap;
 #pragma unroll
     for (int u = 0; u < KEEP_REGS; ++u) {
-      const int64_t i = threadIdx.x + u * SEL_THREADS;
-      r[u] = i < n ? L[i] : make_int2(0, NO_HIT);
+      const uint32_t i = threadIdx.x + u * SEL_THREADS;
+      r[u] = i < nl ? L[i] : make_int2(0, NO_HIT);
     }
   }
-  // g(document, key) of every entry: of the list, or of every hit
-  auto each = [&](auto &&g) {
-    if (in_regs) {
+  for (int i = threadIdx.x; i < 2 * SEL_BINS; i += SEL_THREADS) hist[0][i] = 0;
+  if (threadIdx.x < 2 * CUT_CHUNKS) s_cnt[0][threadIdx.x] = 0;
+  const uint32_t nhit = find_bin<W, PER>(hist1 + q * SEL_BINS, (uint32_t)ncand, wsum[0], &s_bin[0]);
+  const bool cut = nhit > (uint32_t)ncand;  // uniform
+  const uint32_t b1 = cut ? s_bin[0].x : 0, rem1 = (uint32_t)ncand - (cut ? s_bin[0].y : 0);
+  uint32_t T = 0, need = 0;
+  // ties before each chunk, then output offsets, from the chunks' kept and
+  // tied counts in chunk_n (a thread reads those of its own chunks)
+  const int per = (P + SEL_THREADS - 1) / SEL_THREADS;
+  const int c0 = min(P, (int)threadIdx.x * per), c1 = min(P, c0 + per);
+  auto finish = [&]() {
+    uint32_t my = 0, all;
+    for (int c = c0; c < c1; ++c) my += chunk_n[P + c];
+    uint32_t tb = block_scan<W>(my, wsum[3], all);
+    my = 0;
+    for (int c = c0; c < c1; ++c) {
+      const uint32_t t = chunk_n[P + c], take = chunk_n[c] + (tb < need ? min(t, need - tb) : 0);
+      S.counts[3 * (q * P + c) + 1] = tb;
+      S.counts[3 * (q * P + c) + 2] = take;
+      chunk_n[c] = take;
+      tb += t;
+      my += take;
+    }
+    uint32_t off = block_scan<W>(my, wsum[4], all);
+    for (int c = c0; c < c1; ++c) {
+      S.counts[3 * (q * P + c)] = off;
+      off += chunk_n[c];
+    }
+    const uint32_t kept = min(all, (uint32_t)ncand);
+    if (threadIdx.x == 0) {
+      S.st[q] = SelState{0, 0, T, (long long)need, (long long)kept};
+      n_valid[q] = (int32_t)kept;
+    }
+    for (uint32_t i = kept + threadIdx.x; i < (uint32_t)ncand; i += SEL_THREADS) {
+      out_ids[q * ncand + i] = -1;
+      out_keys[q * ncand + i] = 0;
+    }
+  };
+
+  if (one) {
+    // g(document, key) of every entry
+    auto each = [&](auto &&g) {
 #pragma unroll
       for (int u = 0; u < KEEP_REGS; ++u)
         if (r[u].y != NO_HIT) g(r[u].x, fp_key(r[u].y));
-      return;
+    };
+    for (int i = threadIdx.x; i < 2 * P; i += SEL_THREADS) chunk_n[i] = 0;
+    if (cut) {
+      each([&](int, uint32_t u) {
+        if ((u >> 20) == b1) atomicAdd(&hist[0][(u >> 8) & 4095u], 1u);
+      });
+      __syncthreads();
+      find_bin<W, PER>(hist[0], rem1, wsum[1], &s_bin[1]);
+      const uint32_t p2 = (b1 << 12) | s_bin[1].x, rem2 = rem1 - s_bin[1].y;
+      each([&](int, uint32_t u) {
+        if ((u >> 8) == p2) atomicAdd(&hist[1][u & 255u], 1u);
+      });
+      __syncthreads();
+      find_bin<W, PER>(hist[1], rem2, wsum[2], &s_bin[2]);
+      T = (p2 << 8) | s_bin[2].x;
+      need = rem2 - s_bin[2].y;
     }
-    for (int64_t i0 = threadIdx.x; i0 < n; i0 += 4 * SEL_THREADS) {
-      int2 e[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int64_t i = i0 + u * SEL_THREADS;
-        e[u] = make_int2(0, NO_HIT);
-        if (i < n) e[u] = from_list ? L[i] : make_int2((int)i, f[i]);
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (e[u].y != NO_HIT) g(e[u].x, fp_key(e[u].y));
-    }
-  };
-  for (int i = threadIdx.x; i < 2 * P; i += SEL_THREADS) chunk_n[i] = 0;
-  for (int i = threadIdx.x; i < 2 * SEL_BINS; i += SEL_THREADS) hist[0][i] = 0;
-  const uint32_t nhit = find_bin<W, PER>(hist1 + q * SEL_BINS, (uint32_t)ncand, wsum[0], &s_bin[0]);
-  uint32_t T = 0, need = 0;
-  if (nhit > (uint32_t)ncand) {  // uniform
-    const uint32_t b1 = s_bin[0].x, rem1 = (uint32_t)ncand - s_bin[0].y;
-    each([&](int, uint32_t u) {
-      if ((u >> 20) == b1) atomicAdd(&hist[0][(u >> 8) & 4095u], 1u);
+    __syncthreads();  // chunk_n is zero
+    each([&](int d, uint32_t u) {
+      if (u > T) atomicAdd(&chunk_n[d / SEL_CHUNK], 1u);
+      else if (u == T) atomicAdd(&chunk_n[P + d / SEL_CHUNK], 1u);
     });
     __syncthreads();
-    find_bin<W, PER>(hist[0], rem1, wsum[1], &s_bin[1]);
-    const uint32_t p2 = (b1 << 12) | s_bin[1].x, rem2 = rem1 - s_bin[1].y;
-    each([&](int, uint32_t u) {
-      if ((u >> 8) == p2) atomicAdd(&hist[1][u & 255u], 1u);
-    });
+    finish();
+    return;
+  }
+
+  // a long list: this workgroup's chunks, from their part of the list or F'
+  uint32_t p2 = 0, rem2 = 0;
+  if (cut) {
+    find_bin<W, PER>(S.hist2 + q * SEL_BINS, rem1, wsum[1], &s_bin[1]);
+    p2 = (b1 << 12) | s_bin[1].x;
+    rem2 = rem1 - s_bin[1].y;
+    const int g = threadIdx.x / SPLIT_THREADS, t = threadIdx.x % SPLIT_THREADS;
+    const int c = (int)(b % PB) * CUT_CHUNKS + g;
+    uint32_t *h = hist[0] + 256 * g;  // this chunk's histogram of bits 7..0
+    uint32_t above = 0, in = 0;
+    auto count = [&](int32_t x) {
+      if (x == NO_HIT) return;
+      const uint32_t u = fp_key(x);
+      if ((u >> 8) > p2) ++above;
+      else if ((u >> 8) == p2) ++in, atomicAdd(&h[u & 255u], 1u);
+    };
+    if (c < P) {
+      if (nl <= (uint64_t)cap) {  // uniform
+        const uint2 pt = S.part[q * P + c];
+        const int2 *L = S.list + q * cap + pt.x;
+        for (uint32_t i = t; i < pt.y; i += SPLIT_THREADS) count(L[i].y);
+      } else {
+        int32_t x[16];
+        load_fp16(fp + q * ndocs, (int64_t)c * SEL_CHUNK + t * 16, min(ndocs, (int64_t)(c + 1) * SEL_CHUNK), x);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) count(x[i]);
+      }
+    }
+    above = wave_incl_scan(above);
+    in = wave_incl_scan(in);
+    if (lane_id() == 63) {
+      atomicAdd(&s_cnt[g][0], above);
+      atomicAdd(&s_cnt[g][1], in);
+    }
+    __syncthreads();
+    if (c < P) {
+      if (t < 2) store_agent(S.rec + 2 * (q * P + c) + t, s_cnt[g][t]);
+      if (s_cnt[g][1]) {  // (a chunk's counts are at most 4096)
+        if (t < 128) store_agent(S.rows + (q * P + c) * 128 + t, h[2 * t] | h[2 * t + 1] << 16);
+        if (h[t]) atomicAdd(&S.hist3[q * 256 + t], h[t]);
+      }
+    }
+    // the query's last workgroup to get here finds every chunk's record
+    wait_stores();
+    __syncthreads();
+    if (threadIdx.x == 0) s_done = atomicAdd(&S.arrived[q], 1u);
+    __syncthreads();
+    if (s_done != (uint32_t)PB - 1) return;  // uniform
+    if (threadIdx.x < 256) hist[1][threadIdx.x] = load_agent(&S.hist3[q * 256 + threadIdx.x]);
     __syncthreads();
     find_bin<W, PER>(hist[1], rem2, wsum[2], &s_bin[2]);
     T = (p2 << 8) | s_bin[2].x;
     need = rem2 - s_bin[2].y;
+    const uint32_t b3 = T & 255u;
+    // 16 lanes a chunk, 16 of its 256 counts each
+    const uint32_t sub = threadIdx.x & 15;
+    for (int k0 = 0; k0 < P; k0 += SEL_THREADS / 16) {
+      const int k = k0 + (int)(threadIdx.x / 16);
+      uint32_t more = 0, ties = 0;
+      if (k < P) {
+        const uint32_t *rec = S.rec + 2 * (q * P + k), *row = S.rows + (q * P + k) * 128 + 8 * sub;
+        const uint32_t n = load_agent(rec + 1);
+        if (sub == 0) more = load_agent(rec);
+        if (n) {
+          uint32_t y[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) y[i] = load_agent(row + i);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const uint32_t lo = 16 * sub + 2 * i;
+            more += (lo > b3 ? y[i] & 0xFFFFu : 0) + (lo + 1 > b3 ? y[i] >> 16 : 0);
+            ties += lo == b3 ? y[i] & 0xFFFFu : lo + 1 == b3 ? y[i] >> 16 : 0;
+          }
+        }
+      }
+#pragma unroll
+      for (int m = 1; m < 16; m <<= 1) {
+        more += shfl_xor(more, m);
+        ties += shfl_xor(ties, m);
+      }
+      if (k < P && sub == 0) {
+        chunk_n[k] = more;
+        chunk_n[P + k] = ties;
+      }
+    }
+    __syncthreads();
+  } else {
+    // every hit is kept: the chunks' counts are those of the first pass
+    if (b % PB != 0) return;  // uniform
+    for (int k = c0; k < c1; ++k) {
+      chunk_n[k] = S.part[q * P + k].y;
+      chunk_n[P + k] = 0;
+    }
   }
-  each([&](int d, uint32_t u) {
-    if (u > T) atomicAdd(&chunk_n[d / SEL_CHUNK], 1u);
-    else if (u == T) atomicAdd(&chunk_n[P + d / SEL_CHUNK], 1u);
-  });
-  __syncthreads();
-  // ties before each chunk, then output offsets
-  const int per = (P + SEL_THREADS - 1) / SEL_THREADS;
-  const int c0 = min(P, (int)threadIdx.x * per), c1 = min(P, c0 + per);
-  uint32_t my = 0, all;
-  for (int c = c0; c < c1; ++c) my += chunk_n[P + c];
-  uint32_t tb = block_scan<W>(my, wsum[3], all);
-  my = 0;
-  for (int c = c0; c < c1; ++c) {
-    const uint32_t t = chunk_n[P + c], take = chunk_n[c] + (tb < need ? min(t, need - tb) : 0);
-    counts[3 * (q * P + c) + 1] = tb;
-    counts[3 * (q * P + c) + 2] = take;
-    chunk_n[c] = take;
-    tb += t;
-    my += take;
-  }
-  uint32_t off = block_scan<W>(my, wsum[4], all);
-  for (int c = c0; c < c1; ++c) {
-    counts[3 * (q * P + c)] = off;
-    off += chunk_n[c];
-  }
-  const uint32_t kept = min(all, (uint32_t)ncand);
-  if (threadIdx.x == 0) {
-    st[q] = SelState{0, 0, T, (long long)need, (long long)kept};
-    n_valid[q] = (int32_t)kept;
-  }
-  for (uint32_t i = kept + threadIdx.x; i < (uint32_t)ncand; i += SEL_THREADS) {
-    out_ids[q * ncand + i] = -1;
-    out_keys[q * ncand + i] = 0;
-  }
+  finish();
 }
 
 // Per chunk: the ordered compaction of its kept documents, from the chunk's
@@ -1699,33 +1873,34 @@ static int keep_chunks(int64_t nq, int64_t ndocs) {
   return P <= SEL_MAX_CHUNKS && nq * P <= 16384 ? (int)P : 0;
 }
 
-// At least the split select's size whichever is used, so that what fits a
-// fixed scratch does not depend on the choice.
+// The split select's size whichever is used, so that what fits a fixed scratch
+// does not depend on the choice (the small batch's never needs more).
 size_t select_scratch_bytes(int64_t nq, int64_t ndocs, int ncand) {
   const int P = select_chunks(nq, ndocs);
   const size_t cap = (size_t)sel_list_cap(ndocs, P, ncand);
   const size_t split = (size_t)nq * (sizeof(SelState) + (SEL_BINS + 256) * 4 +
                                      (size_t)P * (24 + 256 * 4 + 4 + 4 + cap * 8)) + (size_t)nq * P * (4 + cap * 8) + 1024;
   const int64_t K = keep_chunks(nq, ndocs);
-  const size_t keep = (size_t)nq * (sizeof(SelState) + (size_t)K * (24 + 8) + (size_t)keep_cap(ndocs, ncand) * 8) + 1024;
-  return K ? std::max(split, keep) : split;
+  return K ? std::max(split, small_sel_bytes(nq, K, keep_cap(ndocs, K, ncand))) : split;
 }
 
-void launch_select(const int32_t *fp, const uint32_t *hist, uint32_t *nlist, int64_t nq, int64_t ndocs, int ncand,
-                   void *scratch, int32_t *cand_ids, int32_t *cand_keys, int32_t *n_valid, hipStream_t s) {
+size_t select_zero_bytes(int64_t nq, int64_t ndocs) {
+  return keep_chunks(nq, ndocs) ? (size_t)nq * (SEL_BINS + 256 + 2) * 4 : 0;
+}
+
+void launch_select(const int32_t *fp, const uint32_t *hist, int64_t nq, int64_t ndocs, int ncand, void *scratch,
+                   int32_t *cand_ids, int32_t *cand_keys, int32_t *n_valid, hipStream_t s) {
   if (nq <= 0) return;
   if (const int K = keep_chunks(nq, ndocs)) {
-    const int64_t cap = keep_cap(ndocs, ncand);
-    SelState *st = (SelState *)scratch;
-    long long *counts = (long long *)(st + nq);
-    uint2 *part = (uint2 *)(counts + 3 * nq * K);
-    int2 *list = (int2 *)(part + nq * K);
+    const int64_t cap = keep_cap(ndocs, K, ncand);
+    const SmallSel x = small_sel(scratch, nq, K);
+    const int PB = (K + CUT_CHUNKS - 1) / CUT_CHUNKS;
     const dim3 gc((unsigned)(nq * K)), tb(SPLIT_THREADS);
-    hipLaunchKernelGGL(k_keep_list, gc, tb, 0, s, fp, hist, ndocs, K, ncand, cap, list, nlist, part);
-    hipLaunchKernelGGL(k_keep_cut, dim3((unsigned)nq), dim3(SEL_THREADS), (size_t)K * 8, s, fp, hist, ndocs, K, ncand,
-                       cap, list, nlist, st, counts, cand_ids, cand_keys, n_valid);
-    hipLaunchKernelGGL(k_sel_write, gc, tb, 0, s, fp, ndocs, K, ncand, st, counts, 0, list, (const uint32_t *)nullptr,
-                       nlist, cap, part, cand_ids, cand_keys);
+    hipLaunchKernelGGL(k_keep_list, gc, tb, 0, s, fp, hist, ndocs, K, ncand, cap, x);
+    hipLaunchKernelGGL(k_keep_cut, dim3((unsigned)(nq * (1 + PB))), dim3(SEL_THREADS), (size_t)K * 8, s, fp, hist, nq,
+                       ndocs, K, PB, ncand, cap, x, cand_ids, cand_keys, n_valid);
+    hipLaunchKernelGGL(k_sel_write, gc, tb, 0, s, fp, ndocs, K, ncand, x.st, x.counts, 0, x.list,
+                       (const uint32_t *)nullptr, x.nlist, cap, x.part, cand_ids, cand_keys);
     return;
   }
   if (select_by_query(nq, ndocs)) {

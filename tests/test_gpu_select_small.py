@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+from util_build import product_builder
 from util_gpu import check_search, q_tensor, say, setup
 
 pytestmark = pytest.mark.gpu
@@ -41,3 +42,50 @@ def test_ties_and_long_lists(ncand, k):
     q[1] = 0
     say("ties", ncand, k)
     check_search(idx, oi, q, 32, ncand, k, "bf16", f"ties, ncand {ncand}, k {k}")
+
+
+def _check_prune(idx, oi, q, nprobe, ncand):
+    say("prune", q.shape, nprobe, ncand)
+    cand, keys, nval = (x.cpu().numpy() for x in idx.prune(q_tensor(q, "bf16"), nprobe, ncand))
+    ref = oi.prune(q, nprobe, ncand)
+    for i in range(len(q)):
+        n = ref["n_cand"][i]
+        order = np.argsort(ref["cand"][i, :n])
+        assert nval[i] == n, i
+        assert np.array_equal(cand[i, :n], ref["cand"][i, :n][order]), i
+        assert np.array_equal(keys[i, :n], ref["cand_keys"][i, :n][order]), i
+        assert (cand[i, n:] == -1).all() and (keys[i, n:] == 0).all(), i
+
+
+@pytest.mark.parametrize("ndocs,ncand", [
+    (200_001, 10),       # lists past their capacity: the passes read F'
+    (200_001, 30_000),   # lists longer than the registers, within their capacity
+    (200_001, 199_000),  # every hit kept, from its chunk's count
+    (4096, 1),           # one chunk whose list is past its capacity
+])
+def test_lists_cut_by_many_workgroups(ndocs, ncand):
+    """A tied query, a query of four tokens (few bins of the first pass, so
+    most documents are in the one that is cut) and two of 32, in one batch."""
+    w, c, _, _, oi, idx = setup("tiny", ndocs=ndocs, ncent=64, len_kind=2, len_lo=1, len_hi=3)
+    q, _ = c.queries(4, 32, query_seed=ncand)
+    q[1] = 0
+    q[2, 4:] = 0
+    _check_prune(idx, oi, q, 32, ncand)
+
+
+def test_a_long_list_is_not_cut_by_one_workgroup(monkeypatch):
+    """One query whose million documents all tie: the select's three passes
+    over F' are spread over the chip, well under the 1,600 us that one
+    workgroup takes over them."""
+    monkeypatch.setenv("CHIMERA_STAGE_TIMING", "1")
+    w, c, _, _, _, _ = setup("tiny", ndocs=1_000_000, ncent=64, len_kind=2, len_lo=1, len_hi=2)
+    idx = product_builder(c, w.nbits).upload(0)
+    q = torch.zeros((1, 32, 128), device="cuda")
+    best = {}
+    for ncand in (64, 30_000, 500_000):
+        for _ in range(8):
+            idx.search(q, 32, ncand, 10)
+            best[ncand] = min(best.get(ncand, 1e9), 1e3 * float(idx.stage_times()[3]))
+    say("select of one query, us:", best)
+    assert max(best.values()) < 300, best
+    idx.close()
