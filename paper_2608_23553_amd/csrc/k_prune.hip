@@ -180,7 +180,7 @@ struct WalkLds {
   size_t smask, sfp, bucket, ll, lmask, lsum, skey, scid, dcount, bcnt, bbase, dgm, dgs, dls, nlong, dtab, dtok, dgrp,
       total;
 };
-__host__ __device__ inline WalkLds walk_lds_layout(int R, int mask_bytes, int nprobe, int Tq) {
+__host__ __device__ inline WalkLds walk_lds_layout(int R, int mask_bytes, int nprobe, int Tq, bool tab) {
   const size_t nl = (size_t)nprobe * Tq;
   WalkLds L;
   size_t o = 0;
@@ -206,16 +206,21 @@ __host__ __device__ inline WalkLds walk_lds_layout(int R, int mask_bytes, int np
   L.dgm = take(nl * mask_bytes);
   L.dgs = take(nl * 4);
   L.dls = take(nl);
-  o = o > L.dtab + (4u << WALK_TAB_BITS) ? o : L.dtab + (4u << WALK_TAB_BITS);
+  if (tab) o = o > L.dtab + (4u << WALK_TAB_BITS) ? o : L.dtab + (4u << WALK_TAB_BITS);
   L.nlong = take(12);
-  L.dtok = take(64 * 2);
-  L.dgrp = take(WALK_TAB_BITS * 8);
+  L.dtok = take(tab ? 64 * 2 : 0);
+  L.dgrp = take(tab ? WALK_TAB_BITS * 8 : 0);
   L.total = o;
   return L;
 }
 
-template <typename MaskT, int R, int LPT>
-__global__ __launch_bounds__(WALK_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_cand_walk(
+// TAB: the walk through chains and a table, with the other way for the queries
+// and ranges that it does not take; else every range rank by rank.  (With 128
+// registers, two workgroups a CU; rank by rank with two lists a thread and all
+// the registers it asks for: 186.2 against 190.2 ms for 1024 queries of 32
+// tokens, 1M documents and 32 ranks, where the others gain up to 6%.)
+template <typename MaskT, int R, int LPT, bool TAB>
+__global__ __launch_bounds__(WALK_THREADS) __attribute__((amdgpu_waves_per_eu(TAB || LPT != 2 ? 4 : 1))) void k_cand_walk(
     const int32_t *__restrict__ cent_ids, const int32_t *__restrict__ cent_keys, int64_t nq, int Tq, int TQP,
     int nprobe, const int64_t *__restrict__ ivf_off, const int32_t *__restrict__ ivf_doc, int64_t ndocs, int ncent,
     int ndense, const int8_t *__restrict__ dense_slot, const uint64_t *__restrict__ doc_dense,
@@ -227,7 +232,7 @@ __global__ __launch_bounds__(WALK_THREADS) __attribute__((amdgpu_waves_per_eu(4)
   static_assert(R <= (1 << WALK_DOC_BITS), "a bucket entry holds the document in 13 bits");
   extern __shared__ __align__(16) unsigned char walk_lds[];
   const int nl = nprobe * Tq;
-  const WalkLds lay = walk_lds_layout(R, (int)sizeof(MaskT), nprobe, Tq);
+  const WalkLds lay = walk_lds_layout(R, (int)sizeof(MaskT), nprobe, Tq, TAB);
   MaskT *smask = (MaskT *)(walk_lds + lay.smask);        // [R] tokens already credited, per document
   int32_t *sfp = (int32_t *)(walk_lds + lay.sfp);        // [R] F' accumulators
   uint32_t *bucket = (uint32_t *)(walk_lds + lay.bucket);  // [WALK_BUCKET] the range's entries, by rank
@@ -301,8 +306,10 @@ __global__ __launch_bounds__(WALK_THREADS) __attribute__((amdgpu_waves_per_eu(4)
       dls[r * Tq + k] = dense_slot[c];
       dgm[r * Tq + k] = gm;
       dgs[r * Tq + k] = gs;
-      const int d = atomicAdd(&nlong[1], 1);
-      if (d < WALK_TAB_BITS) ((int2 *)bucket)[d] = make_int2(t, dense_slot[c]);
+      if (TAB) {
+        const int d = atomicAdd(&nlong[1], 1);
+        if (d < WALK_TAB_BITS) ((int2 *)bucket)[d] = make_int2(t, dense_slot[c]);
+      }
       continue;
     }
     const int64_t beg = ivf_off[c], end = ivf_off[c + 1];
@@ -334,8 +341,8 @@ __global__ __launch_bounds__(WALK_THREADS) __attribute__((amdgpu_waves_per_eu(4)
   __syncthreads();
   // the dense groups in rank order, the groups of each token, and the table:
   // entry x is the sum of the best keys of the tokens that the groups of x hold
-  const int ng = nlong[1];
-  bool tab = ng <= WALK_TAB_BITS;  // uniform
+  const int ng = TAB ? nlong[1] : 0;
+  bool tab = TAB && ng <= WALK_TAB_BITS;  // uniform
   if (tab) {
     if ((int)threadIdx.x < ng) {
       const int2 me = ((const int2 *)bucket)[threadIdx.x];
@@ -830,56 +837,64 @@ __global__ __launch_bounds__(WALK_THREADS) __attribute__((amdgpu_waves_per_eu(4)
 size_t walk_lds_bytes(int TQP, int nprobe, int Tq) {
   if ((size_t)nprobe * Tq > (size_t)WALK_MAX_LISTS) return SIZE_MAX;
   // either walk may run (k_walk_lists.hip takes indexes without dense lists)
-  return std::max(walk_lds_layout(walk_range_docs(TQP, nprobe, Tq), TQP == 32 ? 4 : 8, nprobe, Tq).total,
+  return std::max(walk_lds_layout(walk_range_docs(TQP, nprobe, Tq), TQP == 32 ? 4 : 8, nprobe, Tq, false).total,
                   list_walk_lds_bytes(TQP, nprobe, Tq));
 }
 
-template <typename MaskT, int R, int LPT>
+// Whether the walk through chains and a table pays, for workgroups of M
+// ranges.  It saves a barrier and more per rank and range, but its table is
+// built once per workgroup, and costs more the more dense groups a query has:
+// at 1M documents and one range a workgroup (128 queries) it takes 0.86, 0.97
+// and 1.11 of the time rank by rank at 8 ranks with 4, 16 and 32 query tokens,
+// 0.74, 0.84 and 0.93 at 16; with eight ranges (1024 queries) 0.71, 0.76 and
+// 0.99 at 8 ranks, 0.80, 0.87 and 1.03 at 4.  Queries of more than
+// WALK_TAB_BITS dense groups gain nothing: with 64 tokens most have them
+// (1.00 to 1.07 at every rank count), and with few centroids the lower ranks
+// add groups to the tokens' own, about (nprobe - 1) Tq ndense / ncent (100,000
+// documents, 16,384 centroids, 32 tokens: 1.01 at 16 ranks, 1.05 at 32; 1M,
+// 65,536 centroids, 64 ranks: 1.13, where 32 ranks take 0.82).
+bool walk_by_chains(int Tq, int TQP, int nprobe, int ncent, int ndense, int M) {
+  if (TQP != 32 || (int64_t)(nprobe - 1) * Tq * ndense > ncent) return false;
+  if (Tq > 16) return nprobe >= 16 || (nprobe >= 8 && M >= 3);
+  return M * nprobe >= (Tq > 8 ? 12 : 8);
+}
+
+template <typename MaskT, int R, int LPT, bool TAB>
 static void launch_walk_t(const int32_t *cent_ids, const int32_t *cent_keys, int64_t nq, int Tq, int TQP, int nprobe,
                           const int64_t *ivf_off, const int32_t *ivf_doc, int64_t ndocs, int ncent, int ndense,
-                          const int8_t *dense_slot, const uint64_t *doc_dense, const uint64_t *deleted, int32_t *fp, uint32_t *hist,
-                          hipStream_t s) {
-  const int nranges = (int)((ndocs + R - 1) / R);
-  // ranges per workgroup: enough groups per query for about 32768 workgroups
-  // (measured at 8.8M and 1M: shorter workgroups leave fewer CUs idle at a
-  // launch's end than fewer, longer ones; 8.8M walk 403 -> 383 ms, 1M 12.1
-  // -> 10.0 ms, against about 4096)
-  int G = (int)std::min<int64_t>(nranges, std::max<int64_t>(1, (32768 + nq - 1) / nq));
-  const int M = (nranges + G - 1) / G;
-  G = (nranges + M - 1) / M;
+                          const int8_t *dense_slot, const uint64_t *doc_dense, const uint64_t *deleted, int nranges,
+                          int G, int M, int32_t *fp, uint32_t *hist, hipStream_t s) {
   const int64_t blocks = (nq >= 8 ? (nq + 7) / 8 * 8 : nq) * G;
   if (blocks == 0 || nranges == 0) return;
-  const size_t lds = walk_lds_bytes(TQP, nprobe, Tq);
+  const size_t lds = walk_lds_layout(R, (int)sizeof(MaskT), nprobe, Tq, TAB).total;
   static bool attr = [] {
-    return hipFuncSetAttribute((const void *)k_cand_walk<MaskT, R, LPT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    return hipFuncSetAttribute((const void *)k_cand_walk<MaskT, R, LPT, TAB>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                160 * 1024) == hipSuccess;
   }();
   (void)attr;
-  hipLaunchKernelGGL((k_cand_walk<MaskT, R, LPT>), dim3((unsigned)blocks), dim3(WALK_THREADS), lds, s, cent_ids,
+  hipLaunchKernelGGL((k_cand_walk<MaskT, R, LPT, TAB>), dim3((unsigned)blocks), dim3(WALK_THREADS), lds, s, cent_ids,
                      cent_keys, nq, Tq, TQP, nprobe, ivf_off, ivf_doc, ndocs, ncent, ndense, dense_slot, doc_dense,
                      deleted, nranges, G, M, fp, hist);
 }
 
-template <typename MaskT, int R>
-static void launch_walk_r(int lpt, const int32_t *cent_ids, const int32_t *cent_keys, int64_t nq, int Tq, int TQP,
-                          int nprobe, const int64_t *ivf_off, const int32_t *ivf_doc, int64_t ndocs, int ncent,
-                          int ndense, const int8_t *dense_slot, const uint64_t *doc_dense, const uint64_t *deleted, int32_t *fp,
-                          uint32_t *hist, hipStream_t s) {
-  if (lpt <= 1)
-    launch_walk_t<MaskT, R, 1>(cent_ids, cent_keys, nq, Tq, TQP, nprobe, ivf_off, ivf_doc, ndocs, ncent, ndense,
-                               dense_slot, doc_dense, deleted, fp, hist, s);
-  else if (lpt <= 2)
-    launch_walk_t<MaskT, R, 2>(cent_ids, cent_keys, nq, Tq, TQP, nprobe, ivf_off, ivf_doc, ndocs, ncent, ndense,
-                               dense_slot, doc_dense, deleted, fp, hist, s);
-  else
-    launch_walk_t<MaskT, R, 4>(cent_ids, cent_keys, nq, Tq, TQP, nprobe, ivf_off, ivf_doc, ndocs, ncent, ndense,
-                               dense_slot, doc_dense, deleted, fp, hist, s);
+template <typename MaskT, int R, bool TAB>
+static void launch_walk_r(const int32_t *cent_ids, const int32_t *cent_keys, int64_t nq, int Tq, int TQP, int nprobe,
+                          const int64_t *ivf_off, const int32_t *ivf_doc, int64_t ndocs, int ncent, int ndense,
+                          const int8_t *dense_slot, const uint64_t *doc_dense, const uint64_t *deleted, int nranges,
+                          int G, int M, int32_t *fp, uint32_t *hist, hipStream_t s) {
+  const int lpt = (nprobe * Tq + WALK_THREADS - 1) / WALK_THREADS;  // at most 4 (walk_lds_bytes)
+  auto *launch = lpt <= 1   ? launch_walk_t<MaskT, R, 1, TAB>
+                 : lpt <= 2 ? launch_walk_t<MaskT, R, 2, TAB>
+                            : launch_walk_t<MaskT, R, 4, TAB>;
+  launch(cent_ids, cent_keys, nq, Tq, TQP, nprobe, ivf_off, ivf_doc, ndocs, ncent, ndense, dense_slot, doc_dense,
+         deleted, nranges, G, M, fp, hist, s);
 }
 
 void launch_cand_walk(const int32_t *cent_ids, const int32_t *cent_keys, int64_t nq, int Tq, int TQP, int nprobe,
                       const int64_t *ivf_off, const int32_t *ivf_doc, int64_t ndocs, int ncent, int ndense,
                       const int8_t *dense_slot, const uint64_t *doc_dense, const uint64_t *deleted, int32_t *fp, uint32_t *hist,
                       hipStream_t s) {
+  if (nq <= 0) return;
   // without dense lists the centroids are used about evenly: each probed list
   // is walked from memory at its rank (k_walk_lists.hip); measured 2x faster
   // there than the bucketed walk, which wins on skewed (Zipf) lists
@@ -887,13 +902,20 @@ void launch_cand_walk(const int32_t *cent_ids, const int32_t *cent_keys, int64_t
     launch_list_walk(cent_ids, cent_keys, nq, Tq, TQP, nprobe, ivf_off, ivf_doc, ndocs, ncent, deleted, fp, hist, s);
     return;
   }
-  const int lpt = (nprobe * Tq + WALK_THREADS - 1) / WALK_THREADS;  // at most 4 (walk_lds_bytes)
-  if (TQP == 32)
-    launch_walk_r<uint32_t, 4096>(lpt, cent_ids, cent_keys, nq, Tq, TQP, nprobe, ivf_off, ivf_doc, ndocs, ncent,
-                                  ndense, dense_slot, doc_dense, deleted, fp, hist, s);
-  else
-    launch_walk_r<unsigned long long, 2048>(lpt, cent_ids, cent_keys, nq, Tq, TQP, nprobe, ivf_off, ivf_doc, ndocs,
-                                            ncent, ndense, dense_slot, doc_dense, deleted, fp, hist, s);
+  const int R = walk_range_docs(TQP, nprobe, Tq);
+  const int nranges = (int)((ndocs + R - 1) / R);
+  // ranges per workgroup: enough groups per query for about 32768 workgroups
+  // (measured at 8.8M and 1M: shorter workgroups leave fewer CUs idle at a
+  // launch's end than fewer, longer ones; 8.8M walk 403 -> 383 ms, 1M 12.1
+  // -> 10.0 ms, against about 4096)
+  int G = (int)std::min<int64_t>(nranges, std::max<int64_t>(1, (32768 + nq - 1) / nq));
+  const int M = (nranges + G - 1) / std::max(1, G);
+  G = (nranges + M - 1) / std::max(1, M);
+  auto *launch = TQP != 32 ? launch_walk_r<unsigned long long, 2048, false>
+                 : walk_by_chains(Tq, TQP, nprobe, ncent, ndense, M) ? launch_walk_r<uint32_t, 4096, true>
+                                                                     : launch_walk_r<uint32_t, 4096, false>;
+  launch(cent_ids, cent_keys, nq, Tq, TQP, nprobe, ivf_off, ivf_doc, ndocs, ncent, ndense, dense_slot, doc_dense,
+         deleted, nranges, G, M, fp, hist, s);
 }
 
 // ------------------------------------------------------- block helpers

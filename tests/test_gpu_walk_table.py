@@ -3,11 +3,14 @@ through chains of entries and the dense groups' table, ranges with more
 entries than the chains hold (walked rank by rank), queries with more dense
 groups than the table takes, documents with more entries than a lane sorts,
 query tokens that share centroids, both token-mask widths and deletions."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
+from paper_2608_23553_amd import chimera
 from util_gpu import check_search, q_tensor, say, setup
 
 pytestmark = pytest.mark.gpu
@@ -104,3 +107,68 @@ def test_chains_overflow_in_a_workgroups_second_range(row, nprobe):
         assert np.array_equal(cand[0, i].cpu().numpy(), ref["cand"][i, :500][order]), i
         assert np.array_equal(keys[0, i].cpu().numpy(), ref["cand_keys"][i, :500][order]), i
         assert bool((cand[:, i] == cand[0, i]).all()) and bool((keys[:, i] == keys[0, i]).all()), i
+
+
+def _by_chains(Tq, nprobe, ncent, ndense, M):
+    f = chimera.lib()._ZN7chimera14walk_by_chainsEiiiiii
+    f.restype = ctypes.c_bool
+    return f(Tq, 32 if Tq <= 32 else 64, nprobe, ncent, ndense, M)
+
+
+def _dense(c, cl, ndocs, ncent, R=4096):
+    """Documents of each centroid's list in each range of R, and the dense lists."""
+    pairs = np.unique(np.stack([cl, np.repeat(np.arange(ndocs), c.lengths)]), axis=1)
+    count = np.zeros((ncent, -(-ndocs // R)), np.int64)
+    np.add.at(count, (pairs[0], pairs[1] // R), 1)
+    total = count.sum(1)
+    return count, np.nonzero((total * 16 > ndocs) & (np.argsort(np.argsort(-total, kind="stable")) < 64))[0]
+
+
+@pytest.mark.parametrize("ndocs,ncent,nprobe,Tq,lens", [
+    (9001, 65_536, 16, 32, None),        # 10 to 15 dense groups: both ways in one batch; a ragged last range
+    (9001, 65_536, 32, 32, None),        # two lists a thread
+    (4096, 16_384, 16, 16, None),        # one whole range
+    (9001, 8192, 16, 8, (100, 180)),     # some ranges hold more entries than the chains
+    (16_384, 16_384, 16, 16, (60, 160)),
+    (5000, 4096, 9, 7, None),            # few tokens
+])
+def test_prune_by_chains(ndocs, ncent, nprobe, Tq, lens):
+    kw = dict(len_kind=2, len_lo=lens[0], len_hi=lens[1]) if lens else {}
+    w, c, _, cl, oi, idx = setup("1m", ndocs=ndocs, ncent=ncent, **kw)
+    assert _by_chains(Tq, nprobe, ncent, len(_dense(c, cl, ndocs, ncent)[1]), 1)
+    q, _ = c.queries(24, Tq, query_seed=5)
+    q[4] = np.repeat(q[4, :(Tq + 3) // 4], 4, axis=0)[:Tq]  # tokens four times over
+    _check_prune(idx, oi.prune(q, nprobe, ndocs), q, nprobe, ndocs, f"chains: {ndocs} {ncent} {nprobe} {Tq} {lens}")
+
+
+def test_second_range_past_the_chains_by_chains():
+    """A workgroup of two ranges (17,000 queries make it so) whose second holds
+    more entries than the chains: what follows is walked rank by rank."""
+    ndocs = ncent = 16_384
+    w, c, _, cl, oi, idx = setup("1m", ndocs=ndocs, ncent=ncent, len_kind=2, len_lo=50, len_hi=150)
+    count, dense = _dense(c, cl, ndocs, ncent)
+    assert _by_chains(16, 16, ncent, len(dense), 2)
+    few = c.queries(400, 16, query_seed=5)[0][[14, 0, 1, 2, 3]]
+    ids = np.asarray(oracle.probe(oracle.centroid_scores(few[0], c.centroids_k), 16)[0])
+    entries = sum(count[np.setdiff1d(ids[:, r], dense)].sum(0) for r in range(16))
+    assert sum(len(np.intersect1d(ids[:, r], dense)) for r in range(16)) <= 11
+    assert any(entries[a] <= 4096 < entries[a + 1] for a in (0, 2)), entries
+    say("prune 17,000 queries by chains")
+    cand, keys, nval = idx.prune(q_tensor(few, "bf16").repeat(3400, 1, 1), 16, 500)
+    cand, keys, nval = (x.view(3400, 5, *x.shape[1:]) for x in (cand, keys, nval))
+    ref = oi.prune(few, 16, 500)
+    for i in range(5):
+        assert ref["n_cand"][i] == 500 and bool((nval[:, i] == 500).all())
+        order = np.argsort(ref["cand"][i, :500])
+        assert np.array_equal(cand[0, i].cpu().numpy(), ref["cand"][i, :500][order]), i
+        assert np.array_equal(keys[0, i].cpu().numpy(), ref["cand_keys"][i, :500][order]), i
+        assert bool((cand[:, i] == cand[0, i]).all()) and bool((keys[:, i] == keys[0, i]).all()), i
+
+
+@pytest.mark.parametrize("nprobe,Tq", [(8, 64), (24, 64), (32, 64), (8, 32), (24, 32), (64, 32)])
+def test_prune_rank_by_rank(nprobe, Tq):
+    """Either mask width with one, two and four lists a thread."""
+    w, c, _, cl, oi, idx = setup("1m", ndocs=9001, ncent=8192)
+    assert not _by_chains(Tq, nprobe, 8192, len(_dense(c, cl, 9001, 8192)[1]), 1)
+    q, _ = c.queries(9, Tq, query_seed=nprobe)
+    _check_prune(idx, oi.prune(q, nprobe, 9001), q, nprobe, 9001, f"ranks: {nprobe} {Tq}")
