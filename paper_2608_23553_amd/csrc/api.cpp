@@ -354,9 +354,13 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
   };
   // scoring by document where a sub-batch's candidates overlap enough
   // (k_score_docs.hip), by query otherwise
+  auto grouped = [&](int64_t b) {
+    return doc_score_grouped(b, Tq, nprobe, ncand, idx->ndocs, idx->ntok, idx->nnz, idx->max_doc_len, idx->ncent,
+                             idx->ndense, idx->nbits, o.rabitq);
+  };
   bool by_doc = stop == STOP_FULL && (o.rabitq || idx->d_cent16);
   int64_t B = largest_for(by_doc);
-  if (by_doc && !doc_score_grouped(B, idx->ndocs, idx->ntok, idx->ndense, ncand)) {
+  if (by_doc && !grouped(B)) {
     by_doc = false;
     B = largest_for(false);
   }
@@ -382,7 +386,7 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
     // the sub-batches until their scratch fits, down to one query
     while (rc == CHIMERA_E_NOMEM && B > 1) {
       B = (B + 1) / 2;
-      if (by_doc && !doc_score_grouped(B, idx->ndocs, idx->ntok, idx->ndense, ncand)) by_doc = false;
+      if (by_doc && !grouped(B)) by_doc = false;
       need = need_for(B);
       rc = ensure_scratch(idx, need);
     }

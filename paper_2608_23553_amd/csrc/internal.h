@@ -171,12 +171,12 @@ void launch_residual_score(const uint16_t *Qs, int64_t nq, int Tq, int TQP, cons
 // exact in fp16.  f16_tokens_exact: whether they are (n centroid components
 // and the bucket weights, all bf16); f16_of_bf16_grid: grid values of at most
 // 1 in magnitude as fp16 (cent16 is [ncent][128]).  doc_score_grouped: whether
-// the candidates of nq queries overlap enough for it on an index of ntok tokens
-// and ndense dense lists.  scratch holds
-// doc_score_scratch_bytes bytes (no initial contents needed).
+// a batch of nq queries is scored that way (the rule stands at its definition).
+// scratch holds doc_score_scratch_bytes bytes (no initial contents needed).
 bool f16_tokens_exact(const uint16_t *cent, int64_t n, const uint16_t *weights, int nweights);
 void f16_of_bf16_grid(const uint16_t *src, int64_t n, uint16_t *dst);
-bool doc_score_grouped(int64_t nq, int64_t ndocs, int64_t ntok, int ndense, int ncand);
+bool doc_score_grouped(int64_t nq, int Tq, int nprobe, int ncand, int64_t ndocs, int64_t ntok, int64_t nnz,
+                       int max_doc_len, int ncent, int ndense, int nbits, bool rq);
 size_t doc_score_scratch_bytes(int64_t nq, int TQP, int64_t ndocs, int ncand, bool rq);
 void launch_doc_score(const uint16_t *Qs, int64_t nq, int Tq, int TQP, const uint16_t *cent16,
                       const int64_t *doc_off, const int32_t *cid, const uint8_t *codes, int nbits,

@@ -735,21 +735,60 @@ static Visits sort_visits(int64_t nq, int64_t ndocs, const int32_t *cand_ids, co
   return V;
 }
 
-// Scoring by document pays once the visits per document cover its decoding
-// and the launches that sort the visits.  Measured where the two meet (time of
-// the whole search, by document and by query): at 100,000 documents of 64
-// tokens with even popularity 6 visits per document (128 queries of 4096
-// candidates 0.94 against 0.90 ms, 256 queries 1.41 against 1.69 ms); at 1M
-// and 2.2M documents of 70 tokens with dense lists, where popular documents
-// take most visits and S^T is far larger than an L2, 1.8 and 1.3 (256 queries
-// 7.97 against 8.22 ms and 17.1 against 18.4 ms); at 250,000 documents of 320
-// tokens 0.7 (8 queries 4.5 against 5.2 ms, 32 queries 11.3 against 19.6 ms).
-// Documents of one tile have little to share: at 1,000 documents of 32 tokens
-// and 256 visits each 0.167 against 0.157 ms (41 tokens, 5,000 documents, 80
-// visits each: 0.428 against 0.435 ms), so the line is at 36 tokens.
-bool doc_score_grouped(int64_t nq, int64_t ndocs, int64_t ntok, int ndense, int ncand) {
-  const double nv = (double)nq * ncand, per_doc = ndense > 0 ? 2 : 7;
-  return nv >= (1 << 16) && ntok >= 36 * ndocs && nv * (double)ntok >= per_doc * 64 * (double)ndocs * (double)ndocs;
+// Whether a batch goes by document.  Both ways were timed (probe and scoring,
+// as by query the probe also writes S^T) on 20,000 to 2.2M documents, with 4 to
+// 1024 queries of 4 to 64 tokens and 0.5 to 42 visits a document.  Within about
+// a tenth they take, in ns,
+//   by query     30e3 + 0.044 nq ncent B + b V L
+//   by document  78e3 + 0.022 nq ncent B + d D L + 0.0108 B V L + 0.83 ndocs
+// for V visits, D documents with a visit, L tokens a document and B blocks of
+// 32 query tokens.  b is 0.013 at 4 and 0.019 at 32 query tokens (a row of S^T
+// that several tokens share is read once), 0.034 at 64, and 0.025 a block with
+// 4-bit codes; d, the decoding, 0.020 and 0.033.  So few query tokens and few
+// visits a document go by query: by document takes 1.5 times as long with 64
+// queries of 4 tokens and 4096 candidates on 100,000 documents, 1.3 times with
+// 256 and 8192 on 1M, where 32 tokens take 0.96 and 1024 queries 0.73.
+//
+// A visit here is a kept candidate: no more than the probed lists hold, where
+// the lists are about even.
+//
+// One workgroup scores a document, so a document far longer than the others
+// keeps the rest of the chip waiting: with 256 queries of 4096 candidates on
+// 100,000 documents of 64 tokens, one of them of 600, 1200, 8000 and 40,000,
+// by document takes 1.18, 1.66, 5.6 and 26.6 ms, by query 1.34, 1.35, 1.4 and
+// 2.1.  Its chain is as long as its tokens, the rest's share of the chip as
+// long as ncand L / 256; it is left aside below 0.4 of that (0.7 of RaBitQ's,
+// whose scoring by query is slower: a document of 2,400 and 16,384 candidates,
+// 0.93 of the time by query; of 600 and 4096, 0.87; of 2,400 and 4096, 1.72).
+//
+// Besides, by document has to have 2^16 visits, 36 tokens a document (1,000 of
+// 32 tokens and 256 visits each: 0.167 against 0.157 ms) and 7 visits a
+// document of 64 tokens, 2 where there are dense lists.  (Below that line it
+// was up to a third slower with 256 queries and fewer and up to a third faster
+// with 512 and more; those stay by query.)
+//
+// The RaBitQ scoring has no S^T.  By document it takes 0.74 to 0.94 of the
+// time above the same line, but 1.04 to 1.07 with 512 queries of 512
+// candidates: with many queries of 32 tokens their operands no longer stay in
+// an L2, and few candidates each do not make up for it.
+bool doc_score_grouped(int64_t nq, int Tq, int nprobe, int ncand, int64_t ndocs, int64_t ntok, int64_t nnz,
+                       int max_doc_len, int ncent, int ndense, int nbits, bool rq) {
+  if (ndocs <= 0 || ntok < 36 * ndocs) return false;
+  const double n = (double)ndocs, L = (double)ntok / n;
+  const double line = (ndense > 0 ? 2 : 7) * 64 * n / L;
+  if ((double)nq * ncand < (1 << 16) || (double)nq * ncand < line) return false;
+  double kept = ncand;
+  if (ndense == 0) kept = std::min(kept, (double)Tq * nprobe * (double)nnz / ncent);
+  if (max_doc_len > 4 * L && max_doc_len > (rq ? 0.7 : 0.4) * kept * L / 256) return false;
+  if (rq) return Tq > 32 || ncand >= 1024;
+  const double B = Tq > 32 ? 2 : 1, V = (double)nq * kept;
+  const double D = n * (1 - std::exp(-(ndense > 0 ? 0.5 : 1.0) * V / n));
+  const double b = nbits == 4 ? 0.025 + 0.022 * (B - 1) : 0.0127 + 0.0093 * (B - 1) + 0.000185 * Tq;
+  const double by_query = 30e3 + 0.044 * (double)nq * ncent * B + b * V * L;
+  const double by_doc = 78e3 + 0.022 * (double)nq * ncent * B + (nbits == 4 ? 0.033 : 0.020) * D * L +
+                        0.0108 * B * V * L + 0.83 * n;
+  // (20 us in its favour: in small batches it was measured closer than that)
+  return by_doc - 20e3 < by_query;
 }
 
 void launch_doc_score(const uint16_t *Qs, int64_t nq, int Tq, int TQP, const uint16_t *cent16,

@@ -49,3 +49,52 @@ def test_walk_through_chains_where_it_was_measured_faster(chains, Tq, nprobe, nc
     """Indexes of 64 dense lists, workgroups of M ranges."""
     f = _fn("_ZN7chimera14walk_by_chainsEiiiiii", ctypes.c_bool, *[ctypes.c_int] * 6)
     assert f(Tq, 32 if Tq <= 32 else 64, nprobe, ncent, 64, M) == chains
+
+
+_GROUPED = "_ZN7chimera17doc_score_groupedEliiillliiiib"
+
+
+def _grouped(nq, Tq, nprobe, ncand, ndocs, L, ncent, *, longest=180, ndense=0, nbits=2, rq=False):
+    f = _fn(_GROUPED, ctypes.c_bool, I64, I32, I32, I32, I64, I64, I64, I32, I32, I32, I32, ctypes.c_bool)
+    ntok = int(ndocs * L)
+    return f(nq, Tq, nprobe, ncand, ndocs, ntok, ntok, longest, ncent, ndense, nbits, rq)
+
+
+# the corpora that both ways of scoring were timed on: documents, tokens a document, centroids
+EVEN = dict(ndocs=100_000, L=64, ncent=16_384)
+ZIPF = dict(ndocs=100_000, L=64, ncent=16_384, ndense=64)
+M1 = dict(ndocs=1_000_000, L=70, ncent=65_536, ndense=64)
+SHARD = dict(ndocs=2_200_000, L=70, ncent=262_144, ndense=64)
+LONG = dict(ndocs=250_000, L=320, ncent=65_536, longest=512, nbits=4)
+
+
+@pytest.mark.parametrize("by_doc,nq,Tq,nprobe,ncand,on", [
+    # measured faster by document (its time against by query)
+    (True, 256, 32, 4, 4096, EVEN), (True, 1024, 64, 4, 1024, EVEN), (True, 256, 4, 4, 8192, EVEN),  # 0.83 0.76 0.79
+    (True, 256, 32, 4, 2048, ZIPF), (True, 1024, 16, 4, 1024, ZIPF),                                 # 0.94 0.80
+    (True, 1024, 32, 4, 8192, M1), (True, 512, 32, 4, 4096, M1), (True, 1024, 4, 4, 8192, M1),       # 0.73 0.87 0.81
+    (True, 1024, 32, 8, 16_384, SHARD), (True, 512, 8, 8, 16_384, SHARD),                            # 0.68 0.87
+    (True, 128, 64, 8, 8192, LONG), (True, 32, 8, 8, 32_768, LONG),                                  # 0.50 0.72
+    (True, 256, 32, 4, 16_384, dict(EVEN, longest=1200)),                                            # 0.77
+    # measured slower
+    (False, 64, 4, 4, 32_768, EVEN), (False, 64, 8, 4, 32_768, EVEN), (False, 16, 16, 4, 32_768, EVEN),  # 1.37 1.09 1.62
+    (False, 64, 4, 4, 4096, ZIPF), (False, 64, 16, 4, 4096, ZIPF), (False, 64, 32, 4, 4096, ZIPF),   # 1.59 1.31 1.20
+    (False, 256, 4, 4, 2048, ZIPF),                                                                  # 1.11
+    (False, 256, 4, 4, 8192, M1), (False, 256, 16, 4, 8192, M1), (False, 512, 4, 4, 4096, M1),       # 1.38 1.11 1.23
+    (False, 256, 8, 8, 16_384, SHARD), (False, 4, 64, 8, 32_768, LONG),                              # 1.15 1.24
+    # one document keeps the chip waiting
+    (False, 256, 32, 4, 4096, dict(EVEN, longest=1200)), (False, 1024, 32, 4, 4096, dict(EVEN, longest=40_000)),
+    (False, 256, 32, 8, 8192, dict(M1, longest=2000)), (False, 256, 32, 4, 4096, dict(EVEN, L=74.7, longest=600)),
+])
+def test_scoring_by_document_where_it_was_measured_faster(by_doc, nq, Tq, nprobe, ncand, on):
+    assert _grouped(nq, Tq, nprobe, ncand, **on) == by_doc
+
+
+@pytest.mark.parametrize("by_doc,nq,Tq,ncand,on", [
+    (True, 256, 32, 4096, EVEN), (True, 128, 32, 8192, ZIPF), (True, 512, 64, 512, dict(EVEN, ndocs=20_000)),
+    (True, 256, 32, 16_384, dict(EVEN, longest=2400)), (True, 256, 64, 4096, dict(EVEN, longest=600)),
+    (False, 512, 32, 512, dict(EVEN, ndocs=20_000)), (False, 512, 32, 512, ZIPF),  # 1.07 1.04
+    (False, 256, 64, 4096, dict(EVEN, longest=2400)), (False, 256, 32, 4096, dict(EVEN, longest=2400)),  # 1.41 1.72
+])
+def test_rabitq_scoring_by_document_where_it_was_measured_faster(by_doc, nq, Tq, ncand, on):
+    assert _grouped(nq, Tq, 4, ncand, **on, rq=True) == by_doc

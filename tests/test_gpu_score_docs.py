@@ -4,13 +4,15 @@ of 32 and one more, more tiles than the kernel keeps at once, odd and many
 visits, both code widths, one and two blocks of query tokens.  300 queries
 keep 250 or more of 300 documents, so each document has far more visits than
 the rule asks for."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
 import synth
-from paper_2608_23553_amd import build_index
+from paper_2608_23553_amd import build_index, chimera
 from synth import k_to_bf16_bits
 from util_corpus import rand_grid
 from util_build import product_builder
@@ -65,4 +67,144 @@ def test_rabitq_by_document(Tq, lo, hi):
         ref = oracle.search_rabitq(oi, q[i:i + 1], 16, 300, 40, signs, 4, codes, g1)
         assert np.array_equal(ids[i].cpu().numpy(), ref["ids"][0]), i
         assert np.array_equal(scores[i].cpu().numpy(), ref["scores"][0]), i
+    idx.close()
+
+
+def _goes_by_document(idx, nq, Tq, nprobe, ncand, nbits=2, rq=False):
+    """The library's rule, for these corpora of 64 centroids (every list is dense)."""
+    f = chimera.lib()._ZN7chimera17doc_score_groupedEliiillliiiib
+    i32, i64 = ctypes.c_int32, ctypes.c_int64
+    f.restype, f.argtypes = ctypes.c_bool, [i64, i32, i32, i32, i64, i64, i64, i32, i32, i32, i32, ctypes.c_bool]
+    i = idx.info()
+    return f(nq, Tq, nprobe, ncand, i["ndocs"], i["ntokens"], i["nnz"], i["max_doc_len"], i["ncent"], 64, nbits, rq)
+
+
+def _np(out):
+    torch.cuda.synchronize()
+    return [t.cpu().numpy() for t in out]
+
+
+def _by_query(search, Q, nprobe, ncand, k, step):
+    """The same searches in batches too small to go by document."""
+    parts = [_np(search(Q[i:i + step], nprobe, ncand, k)) for i in range(0, len(Q), step)]
+    return [np.concatenate(x) for x in zip(*parts)]
+
+
+@pytest.mark.parametrize("nbits", [2, 4])
+@pytest.mark.parametrize("Tq,lo,hi", [(5, 1, 80), (32, 31, 65), (32, 150, 420), (33, 1, 80), (64, 120, 420)])
+def test_by_document_is_by_query(nbits, Tq, lo, hi):
+    """1,000 queries of 299 candidates at once and 200 at a time, bit for bit,
+    and sampled ones against the oracle."""
+    w, c, k, cl, oi, idx = setup("tiny", ndocs=300, ncent=64, nbits=nbits, len_kind=2, len_lo=lo, len_hi=hi)
+    assert _goes_by_document(idx, 1000, Tq, 16, 299, nbits) and not _goes_by_document(idx, 200, Tq, 16, 299, nbits)
+    q, _ = c.queries(1000, Tq, query_seed=Tq + lo)
+    Q = q_tensor(q, "bf16")
+    say("by document and by query", nbits, Tq, lo, hi)
+    ids, scores = _np(idx.search(Q, 16, 299, 40))
+    ids2, scores2 = _by_query(idx.search, Q, 16, 299, 40, 200)
+    assert np.array_equal(ids, ids2) and np.array_equal(scores, scores2)
+    sample = [0, 7, 500, 999]
+    ref = oi.search(q[sample], 16, 299, 40)
+    assert np.array_equal(ids[sample], ref["ids"]) and np.array_equal(scores[sample], ref["scores"])
+
+
+@pytest.mark.parametrize("Tq,lo,hi", [(5, 1, 80), (32, 31, 65), (32, 150, 300), (64, 120, 260)])
+def test_rabitq_by_document_is_by_query(Tq, lo, hi):
+    w, c, k, cl, oi, _ = setup("tiny", ndocs=1100, ncent=64, len_kind=2, len_lo=lo, len_hi=hi)
+    signs = synth.rotation_signs(31)
+    idx = product_builder(c, w.nbits, rabitq_signs=signs).upload(0)
+    assert _goes_by_document(idx, 90, Tq, 16, 1099, rq=True) and not _goes_by_document(idx, 45, Tq, 16, 1099, rq=True)
+    codes, _, g1 = oracle.rabitq_encode(k, signs, 4)
+    q, _ = c.queries(90, Tq, query_seed=Tq + lo)
+    q[3] = 0
+    Q = q_tensor(q, "bf16")
+    say("rabitq by document and by query", Tq, lo, hi)
+    ids, scores = _np(idx.search_rabitq(Q, 16, 1099, 40))
+    ids2, scores2 = _by_query(idx.search_rabitq, Q, 16, 1099, 40, 45)
+    assert np.array_equal(ids, ids2) and np.array_equal(scores, scores2)
+    sample = [0, 3, 89]
+    ref = oracle.search_rabitq(oi, q[sample], 16, 1099, 40, signs, 4, codes, g1)
+    assert np.array_equal(ids[sample], ref["ids"]) and np.array_equal(scores[sample], ref["scores"])
+    idx.close()
+
+
+def _fresh(monkeypatch, c, nbits, **kw):
+    """An index of its own (no arena yet) that counts its sub-batches."""
+    monkeypatch.setenv("CHIMERA_STAGE_TIMING", "1")
+    return product_builder(c, nbits, **kw).upload(0)
+
+
+def _passes(idx, nq):
+    """Queries of a sub-batch of the last search, and its number of sub-batches."""
+    n = int(idx.stage_times()[6])
+    return -(-nq // n), n
+
+
+def test_sub_batches_by_document(monkeypatch):
+    """Several sub-batches that go by document, the last one shorter, residual
+    and RaBitQ; the same as in one pass."""
+    w, c, _, _, _, one = setup("tiny", ndocs=1100, ncent=64, len_kind=2, len_lo=31, len_hi=65)
+    signs = synth.rotation_signs(31)
+    idx = _fresh(monkeypatch, c, w.nbits, rabitq_signs=signs)
+    q, _ = c.queries(391, 32, query_seed=77)
+    Q = q_tensor(q, "bf16")
+    want = _np(one.search(Q, 16, 1099, 40))
+    want_rq = _np(idx.search_rabitq(Q, 16, 1099, 40))
+    assert _passes(idx, 391) == (391, 1)
+    monkeypatch.setenv("CHIMERA_SCRATCH_MB", "16")
+    for rq, search, ref in ((False, idx.search, want), (True, idx.search_rabitq, want_rq)):
+        say("sub-batches by document", rq)
+        got = _np(search(Q, 16, 1099, 40))
+        B, n = _passes(idx, 391)
+        say(n, "sub-batches of", B)
+        assert n > 1 and 391 % B and _goes_by_document(idx, B, 32, 16, 1099, rq=rq)
+        assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
+    idx.close()
+
+
+def test_arena_that_does_not_fit_by_document(monkeypatch):
+    """Sub-batches halved because the device refuses the arena: once with the
+    halves still by document, and down to where they go by query (whose S^T
+    then enters the scratch)."""
+    w, c, _, _, _, one = setup("tiny", ndocs=300, ncent=64, len_kind=2, len_lo=31, len_hi=65)
+    q, _ = c.queries(700, 32, query_seed=78)
+    Q = q_tensor(q, "bf16")
+    want = _np(one.search(Q, 16, 300, 40))
+    routes = {}
+    for mb in (48, 32, 16, 8):
+        idx = _fresh(monkeypatch, c, w.nbits)
+        monkeypatch.setenv("CHIMERA_SCRATCH_DEVICE_MB", str(mb))
+        got = _np(idx.search(Q, 16, 300, 40))
+        monkeypatch.delenv("CHIMERA_SCRATCH_DEVICE_MB")
+        B, n = _passes(idx, 700)
+        routes[n, _goes_by_document(idx, B, 32, 16, 300)] = mb
+        say(mb, "MB:", n, "sub-batches of", B)
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+        idx.close()
+    assert any(n > 1 and docs for n, docs in routes) and any(not docs for _, docs in routes), routes
+
+
+def test_by_document_with_deletions_and_without_allocation():
+    w, c, _, _, oi, _ = setup("tiny", ndocs=300, ncent=64, len_kind=2, len_lo=31, len_hi=65)
+    idx = product_builder(c, w.nbits).upload(0)
+    gone = np.zeros(300, bool)
+    gone[np.random.default_rng(9).choice(300, 40, replace=False)] = True
+    idx.delete(np.nonzero(gone)[0])
+    assert _goes_by_document(idx, 600, 32, 16, 299)
+    q, _ = c.queries(600, 32, query_seed=79)
+    Q = q_tensor(q, "bf16")
+    for label in ("bitmap", "compacted"):
+        say("by document,", label)
+        ids, scores = _np(idx.search(Q, 16, 299, 40))
+        na = torch.full((600, 40), -7, dtype=torch.int32, device="cuda"), torch.zeros((600, 40), device="cuda")
+        rc = chimera.lib().chimera_search_noalloc(idx._h, Q.data_ptr(), chimera.BF16, 600, 32, 128, 16, 299, 40,
+                                                  na[0].data_ptr(), na[1].data_ptr(),
+                                                  torch.cuda.current_stream().cuda_stream)
+        assert rc == chimera.OK, chimera.last_error()
+        na = _np(na)
+        assert np.array_equal(ids, na[0]) and np.array_equal(scores, na[1])
+        sample = [0, 299, 599]
+        ref = oracle.search_deleted(oi, q[sample], 16, 299, 40, gone)
+        assert np.array_equal(ids[sample], ref["ids"])
+        idx.compact()
     idx.close()
