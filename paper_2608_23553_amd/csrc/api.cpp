@@ -377,16 +377,21 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
       if (one > fixed.bytes) need = std::max(need, one), B = 1;
     }
     while (need > fixed.bytes && B > 1) need = need_for(--B);
+    if (need > fixed.bytes && by_doc) {  // and may fit so when it does not by document
+      by_doc = false;
+      need = need_for(B);
+    }
     if (need > fixed.bytes)
       return fail(CHIMERA_E_UNSUPPORTED, "one query of this search needs %zu bytes of scratch, more than the "
                   "fixed scratch's %zu", need, fixed.bytes);
   } else {
     int rc = ensure_scratch(idx, need);
     // the device cannot hold that much now (other allocations on it): halve
-    // the sub-batches until their scratch fits, down to one query
-    while (rc == CHIMERA_E_NOMEM && B > 1) {
+    // the sub-batches until their scratch fits, down to one query (by document
+    // or, with few centroids, only by query)
+    while (rc == CHIMERA_E_NOMEM && (B > 1 || by_doc)) {
+      if (by_doc && (B == 1 || !grouped((B + 1) / 2))) by_doc = false;
       B = (B + 1) / 2;
-      if (by_doc && !grouped(B)) by_doc = false;
       need = need_for(B);
       rc = ensure_scratch(idx, need);
     }

@@ -184,6 +184,24 @@ def test_arena_that_does_not_fit_by_document(monkeypatch):
     assert any(n > 1 and docs for n, docs in routes) and any(not docs for _, docs in routes), routes
 
 
+def test_one_query_that_fits_by_query_only(monkeypatch):
+    """One query that keeps all of 66,000 documents goes by document, which
+    needs two words a document more than the centroid scores of 64 centroids:
+    where the device has only the latter, it is answered by query."""
+    w = synth.WORKLOADS["tiny"].scaled(ndocs=66_000, ncent=64, nbits=4, len_kind=0, len_lo=132, len_hi=132)
+    c = synth.Corpus(w.corpus_spec())
+    idx = _fresh(monkeypatch, c, 4)
+    assert _goes_by_document(idx, 1, 64, 32, 66_000, 4)
+    q, _ = c.queries(1, 64, query_seed=3)
+    Q = q_tensor(q, "bf16")
+    monkeypatch.setenv("CHIMERA_SCRATCH_DEVICE_MB", "3")
+    got = _np(idx.search(Q, 32, 66_000, 40))
+    monkeypatch.delenv("CHIMERA_SCRATCH_DEVICE_MB")
+    want = _np(idx.search(Q, 32, 66_000, 40))
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    idx.close()
+
+
 def test_by_document_with_deletions_and_without_allocation():
     w, c, _, _, oi, _ = setup("tiny", ndocs=300, ncent=64, len_kind=2, len_lo=31, len_hi=65)
     idx = product_builder(c, w.nbits).upload(0)
