@@ -17,8 +17,10 @@
 // to 1 in magnitude exactly, so the sum is exact whenever max |c_d| + max |w|
 // <= 1 (f16_tokens_exact; the caller checks it once per index and keeps to
 // k_score.hip otherwise).  Query components are bf16 grid values, exact in
-// fp16 as well, and the products are summed in fp32, exact in any order under
-// the same norm bound as before.  The scores are the same bits.
+// fp16 as well (the norm bound of exact scores, 4 / (max |c| + sqrt(128) max
+// |w|), is at most 8192 as soon as one c or w is not 0), and the products are
+// summed in fp32, exact in any order under that bound.  The scores are the
+// same bits.
 //
 // Steps: k_visit_count takes each visit's rank within its document (one
 // atomic per visit), k_visit_alloc gives every document a slice of the visit
@@ -60,7 +62,8 @@ bool f16_tokens_exact(const uint16_t *cent, int64_t n, const uint16_t *weights, 
   int32_t cmax = 0, wmax = 0;
   for (int64_t i = 0; i < n; ++i) cmax = std::max(cmax, std::abs(grid_k_of_float(float_of_bf16(cent[i]))));
   for (int u = 0; u < nweights; ++u) wmax = std::max(wmax, std::abs(grid_k_of_float(float_of_bf16(weights[u]))));
-  return cmax + wmax <= 2048;
+  // (all zero: such an index bounds no query's norm, whose components then need not fit fp16)
+  return cmax + wmax > 0 && cmax + wmax <= 2048;
 }
 
 void f16_of_bf16_grid(const uint16_t *src, int64_t n, uint16_t *dst) {

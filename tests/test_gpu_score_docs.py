@@ -226,3 +226,20 @@ def test_by_document_with_deletions_and_without_allocation():
         assert np.array_equal(ids[sample], ref["ids"])
         idx.compact()
     idx.close()
+
+
+def test_an_index_of_zeros_takes_any_query():
+    """Centroids and weights of 0 bound no query's norm, so its components may
+    be past fp16: every score is 0, in a batch as for one query."""
+    lens = np.full(300, 48, np.int32)
+    tok = np.zeros((300 * 48, 128), np.uint16)
+    cid = (np.arange(len(tok)) % 64).astype(np.int32)
+    idx = build_index(np.zeros((64, 128), np.uint16), 2, lambda: [(tok, cid, lens)]).upload(0)
+    assert idx.info()["q_norm_limit"] > 1e8 and _goes_by_document(idx, 600, 31, 16, 299)
+    Q = torch.full((600, 31, 128), 1e6, device="cuda")
+    say("zeros")
+    one = _np(idx.search(Q[:1], 16, 299, 40))
+    ids, scores = _np(idx.search(Q, 16, 299, 40))
+    assert (one[1] == 0).all() and (scores == 0).all()
+    assert (ids == one[0]).all()
+    idx.close()
