@@ -91,9 +91,11 @@ static int upload(const HostIndex &h, int device, chimera_index **out) {
   std::vector<int64_t> tok_off;
   std::vector<int32_t> ivf_tok, tok_doc;
   token_lists(h, tok_off, ivf_tok, tok_doc);
+  std::vector<uint16_t> cent_op((size_t)probe_operand_size(h.ncent));
+  probe_operand(h.cent.data(), h.ncent, cent_op.data());
   struct Sec { void **dst; const void *src; size_t bytes; size_t pad; };
   std::vector<Sec> secs = {
-      {(void **)&idx->d_cent, h.cent.data(), h.cent.size() * 2},
+      {(void **)&idx->d_cent, cent_op.data(), cent_op.size() * 2},
       {(void **)&idx->d_doc_off, h.doc_off.data(), h.doc_off.size() * 8},
       {(void **)&idx->d_cid, h.cid.data(), h.cid.size() * 4},
       {(void **)&idx->d_codes, h.codes.data(), h.codes.size()},
@@ -122,9 +124,6 @@ static int upload(const HostIndex &h, int device, chimera_index **out) {
     secs.push_back({(void **)&idx->d_rq_g1, h.rq_g1.data(), h.rq_g1.size() * 4, (size_t)kTokenPad * 4 + 256});
     secs.push_back({(void **)&idx->d_rq_signs, h.rq_signs.data(), h.rq_signs.size(), 256});
   }
-  std::vector<uint16_t> cent_op((size_t)probe_operand_size(h.ncent));
-  probe_operand(h.cent.data(), h.ncent, cent_op.data());
-  secs.push_back({(void **)&idx->d_cent_op, cent_op.data(), cent_op.size() * 2, 256});
   std::vector<uint16_t> cent16;
   if (f16_tokens_exact(h.cent.data(), (int64_t)h.cent.size(), h.weights.data(), (int)h.weights.size())) {
     cent16.resize(h.cent.size());
@@ -434,7 +433,7 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
     stage_mark(idx, s, mark);
     launch_round_queries(Qb, q_dtype, nb, Tq, TQP, Qs, s);
     stage_mark(idx, s, mark);
-    launch_probe(Qs, rows, TQP, idx->d_cent_op, idx->ncent, plan, nprobe, part, ST, s);
+    launch_probe(Qs, rows, TQP, idx->d_cent, idx->ncent, plan, nprobe, part, ST, s);
     launch_probe_merge(part, nb, Tq, TQP, plan, nprobe, ci, ck, s);
     CHIMERA_HIP(hipGetLastError());
     if (stop == STOP_PROBE) {
@@ -570,7 +569,7 @@ void chimera_index_free(chimera_index *idx) {
   void *ptrs[] = {idx->d_cent,    idx->d_doc_off,    idx->d_cid,       idx->d_codes,     idx->d_ivf_off,
                   idx->d_ivf_doc, idx->d_dense_slot, idx->d_doc_dense, idx->d_tok_off,   idx->d_ivf_tok,
                   idx->d_tok_doc, idx->scratch,      idx->d_check,     idx->d_deleted,   idx->d_rq_bits,
-                  idx->d_rq_g1,   idx->d_rq_signs,   idx->d_cent16,    idx->d_cent_op};
+                  idx->d_rq_g1,   idx->d_rq_signs,   idx->d_cent16};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   collab_free(idx);
@@ -639,7 +638,11 @@ int chimera_index_compact(chimera_index *idx) {
     h.ndocs = idx->ndocs;
     const int64_t cb = (int64_t)idx->dim * idx->nbits / 8;
     h.cent.resize((size_t)idx->ncent * idx->dim);
-    CHIMERA_HIP(hipMemcpy(h.cent.data(), idx->d_cent, h.cent.size() * 2, hipMemcpyDeviceToHost));
+    {
+      std::vector<uint16_t> op((size_t)probe_operand_size(idx->ncent));
+      CHIMERA_HIP(hipMemcpy(op.data(), idx->d_cent, op.size() * 2, hipMemcpyDeviceToHost));
+      probe_rows(op.data(), idx->ncent, h.cent.data());
+    }
     h.cut_k.assign(idx->h_cut, idx->h_cut + (1 << idx->nbits) - 1);
     h.weights.assign(idx->h_weights, idx->h_weights + (1 << idx->nbits));
     std::vector<int32_t> cid((size_t)idx->ntok);
@@ -702,14 +705,12 @@ int chimera_index_compact(chimera_index *idx) {
                      (void **)&idx->d_codes,     (void **)&idx->d_ivf_off,    (void **)&idx->d_ivf_doc,
                      (void **)&idx->d_dense_slot, (void **)&idx->d_doc_dense, (void **)&idx->d_tok_off,
                      (void **)&idx->d_ivf_tok,   (void **)&idx->d_tok_doc,    (void **)&idx->d_rq_bits,
-                     (void **)&idx->d_rq_g1,     (void **)&idx->d_rq_signs,   (void **)&idx->d_cent16,
-                     (void **)&idx->d_cent_op};
+                     (void **)&idx->d_rq_g1,     (void **)&idx->d_rq_signs,   (void **)&idx->d_cent16};
     void **theirs[] = {(void **)&fresh->d_cent,      (void **)&fresh->d_doc_off,    (void **)&fresh->d_cid,
                        (void **)&fresh->d_codes,     (void **)&fresh->d_ivf_off,    (void **)&fresh->d_ivf_doc,
                        (void **)&fresh->d_dense_slot, (void **)&fresh->d_doc_dense, (void **)&fresh->d_tok_off,
                        (void **)&fresh->d_ivf_tok,   (void **)&fresh->d_tok_doc,    (void **)&fresh->d_rq_bits,
-                       (void **)&fresh->d_rq_g1,     (void **)&fresh->d_rq_signs,   (void **)&fresh->d_cent16,
-                       (void **)&fresh->d_cent_op};
+                       (void **)&fresh->d_rq_g1,     (void **)&fresh->d_rq_signs,   (void **)&fresh->d_cent16};
     for (size_t i = 0; i < sizeof(mine) / sizeof(mine[0]); ++i) {
       if (*mine[i]) (void)hipFree(*mine[i]);
       *mine[i] = *theirs[i];

@@ -94,7 +94,8 @@ void launch_check_queries(const void *Q, int q_dtype, int64_t ntokens, double li
                           hipStream_t s);
 
 // Probe: S = Qs * cent^T on MFMA, top-nprobe per row.  rows = nq*TQP.
-// cop is probe_operand's copy of the centroids (probe_operand_size values).
+// cop holds the centroids in probe_operand's order (probe_operand_size values;
+// probe_rows: back to rows).
 // part: [nsplit][rows][pmax] u64 partial lists.  ST (optional): [nq][ncent][TQP] f32.
 struct ProbePlan {
   int pmax = 0, nsplit = 0, tiles_per_split = 0;
@@ -104,6 +105,7 @@ ProbePlan plan_probe(int64_t rows, int ncent, int nprobe);
 size_t probe_part_bytes(const ProbePlan &p, int64_t rows);
 int64_t probe_operand_size(int ncent);
 void probe_operand(const uint16_t *cent, int ncent, uint16_t *out);
+void probe_rows(const uint16_t *cop, int ncent, uint16_t *cent);
 void launch_probe(const uint16_t *Qs, int64_t rows, int TQP, const uint16_t *cop, int ncent,
                   const ProbePlan &p, int nprobe, uint64_t *part, float *ST, hipStream_t s);
 // Merge partial lists into cent_ids/cent_keys [nq][TQP][nprobe] (rows j < Tq).
@@ -245,8 +247,7 @@ struct chimera_index {
   int32_t ncent = 0, dim = 0, nbits = 0, max_doc_len = 0;
   int64_t ndocs = 0, ntok = 0, nnz = 0;
   int64_t device_bytes = 0;
-  uint16_t *d_cent = nullptr;
-  uint16_t *d_cent_op = nullptr;  // centroids in the probe's operand order (probe_operand)
+  uint16_t *d_cent = nullptr;    // centroids in the probe's operand order (probe_operand)
   uint16_t *d_cent16 = nullptr;  // centroids as fp16 [ncent][dim], or null (see f16_tokens_exact)
   int64_t *d_doc_off = nullptr;
   int32_t *d_cid = nullptr;

@@ -159,6 +159,12 @@ void probe_operand(const uint16_t *cent, int ncent, uint16_t *out) {
         std::copy_n(cent + c * 128 + 64 * (l >> 5) + 8 * s, 8, out + ((8 * t + s) * 64 + l) * 8);
       }
 }
+void probe_rows(const uint16_t *cop, int ncent, uint16_t *cent) {
+  for (int64_t c = 0; c < ncent; ++c)
+    for (int s = 0; s < 8; ++s)
+      for (int h = 0; h < 2; ++h)
+        std::copy_n(cop + ((8 * (c >> 5) + s) * 64 + 32 * h + (c & 31)) * 8, 8, cent + c * 128 + 64 * h + 8 * s);
+}
 int64_t probe_operand_size(int ncent) { return (int64_t)((ncent + 31) / 32) * 4096; }
 
 // One workgroup: 32 query rows (one column block) x a range of centroid tiles.

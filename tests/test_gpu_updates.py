@@ -106,3 +106,16 @@ def test_collab_search_with_deletions_and_compaction():
         assert np.array_equal(gs, ref["scores"]), label
         assert np.array_equal(gn, ref["n_full"]), label
     idx.close()
+
+
+@pytest.mark.parametrize("ncent,dense_lists", [(1025, False), (65, True)])
+def test_device_sections(ncent, dense_lists):
+    """device_bytes is the sections' size: the centroids once in the probe's
+    order (whole tiles of 32) and once as fp16, and everything else once."""
+    w, c, _, _, _, idx = setup("tiny", ncent=ncent)
+    i = idx.info()
+    n, t, z = i["ndocs"], i["ntokens"], i["nnz"]
+    cents = -(-ncent // 32) * 32 * 256 + ncent * 256
+    lists = (ncent + 1) * 8 + z * 4 + (ncent + 1) * 8 + t * 8  # of documents, of tokens with their documents
+    dense = ncent + (n * 8 if dense_lists else 0)
+    assert i["device_bytes"] == cents + (n + 1) * 8 + t * (4 + 16 * w.nbits) + lists + dense
