@@ -41,10 +41,10 @@ HBM_PEAK_GBS = 8000.0
 BF16_PEAK_TFLOPS = 2500.0
 STAGES = ["round", "probe", "walk", "select", "score", "topk"]
 RABITQ_SEED = 20260
-KERNEL_OF_STAGE = {"probe": "k_probe", "walk": "k_cand_walk", "select": "k_select", "score": "k_residual_score",
+KERNEL_OF_STAGE = {"probe": "k_probe", "walk": "k_cand_walk", "select": "k_select", "score": "k_doc_score",
                    "topk": "k_topk", "round": "k_round_queries"}
 SOURCE_OF_STAGE = {"probe": "k_probe.hip", "walk": "k_prune.hip", "select": "k_prune.hip",
-                   "score": "k_score.hip", "topk": "k_score.hip", "round": "k_probe.hip"}
+                   "score": "k_score_docs.hip", "topk": "k_score.hip", "round": "k_probe.hip"}
 
 
 def host_memory_fits(nbytes: int, cap: float = 240 * 2**30):

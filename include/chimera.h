@@ -91,9 +91,8 @@ enum { CHIMERA_F32 = 0, CHIMERA_BF16 = 1 };
 enum { CHIMERA_REFINE_CENTROID = 0, CHIMERA_REFINE_TOKEN = 1 };
 
 /* Limits of this build.  Besides these, the candidate walk keeps per-list
- * state for all Tq x nprobe probed lists of a query on chip: with more than
- * 32 query tokens, Tq * nprobe up to 2304 always fits (e.g. 64 x 32), and
- * larger products may return CHIMERA_E_UNSUPPORTED. */
+ * state for all Tq x nprobe probed lists of a query on chip: Tq * nprobe up to
+ * 2048 fits (e.g. 64 x 32), larger products return CHIMERA_E_UNSUPPORTED. */
 #define CHIMERA_DIM 128
 #define CHIMERA_MAX_TQ 64
 #define CHIMERA_MAX_NPROBE 64

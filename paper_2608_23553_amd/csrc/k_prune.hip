@@ -36,21 +36,19 @@ void launch_fill_zero(void *p, size_t bytes, hipStream_t s) {
 // Workgroup (query q, group g): the document ranges [d0, d0 + R) of a
 // contiguous group of ranges, one after the other, in one of two ways.
 //
-// Through chains and a table, where the query has at most WALK_TAB_BITS dense
-// groups (below): F' is a maximum per query token, so it needs no order.  The
-// dense groups' own F' is a table of 2^g sums, built once per workgroup, that
-// a document looks up by the bits of its dense mask.  Every posting entry of
-// the range is linked into its document's chain in LDS; documents with a chain
-// (about a quarter on Zipf-popular corpora) are listed and taken one a lane:
-// up to four entries are sorted by rank and each corrects the table's sum for
-// the tokens that no better entry or dense group holds; longer chains are
-// taken by the whole wave, a query token a lane.  Two barriers a range, where
-// the other way has one a rank and more; the group's histogram is kept in LDS
-// and added once.  1024 queries x 2.2M documents, 16 ranks: 23.8 -> 20.3 ms; 1M
-// documents, 8 ranks: 10.0 ms either way (10.8 rank by rank in this kernel,
-// whose registers are cut to 128 for two workgroups a CU).  The limit is now
-// the instructions and LDS round trips of each range (the VALU is busy 44% of
-// the time, the address units a third).
+// Through chains and a table, where walk_by_chains says so and the query has at
+// most WALK_TAB_BITS dense groups (below): F' is a maximum per query token, so
+// it needs no order.  The dense groups' own F' is a table of 2^g sums, built
+// once per workgroup, that a document looks up by the bits of its dense mask.
+// Every posting entry of the range is linked into its document's chain in LDS;
+// documents with a chain (about a quarter on Zipf-popular corpora) are listed
+// and taken one a lane: up to four entries are sorted by rank and each corrects
+// the table's sum for the tokens that no better entry or dense group holds;
+// longer chains are taken by the whole wave, a query token a lane.  Three
+// barriers a range (the chains are complete; the range has been read; the entry
+// counter is cleared), where the other way has one a rank and more; the group's
+// histogram is kept in LDS and added once.  1024 queries x 2.2M documents, 16
+// ranks: 23.8 -> 20.3 ms; 1M documents, 8 ranks: 10.0 ms either way.
 //
 // Rank by rank, else, and from the first range on that holds more entries than
 // the chains take (WALK_NODES).  The state of a range
