@@ -110,11 +110,11 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t x, uint32_t *wsum, uint3
 
 // Radix-select step over the 64 W PER bins of `bins` (16-byte aligned), from the
 // highest bin down, by a block of W waves: the bin where the running count
-// reaches rem (0 < rem <= total) and the count above it; without such a bin
-// (total < rem) found.x stays as it was.  Returns the total.  found and wsum
+// reaches rem (0 < rem <= total), the count above it and its own; without such
+// a bin (total < rem) found stays as it was.  Returns the total.  found and wsum
 // are shared; both are free for the next call after a barrier.
 template <int W, int PER>
-__device__ __forceinline__ uint32_t find_bin(const uint32_t *bins, uint32_t rem, uint32_t *wsum, uint2 *found) {
+__device__ __forceinline__ uint32_t find_bin(const uint32_t *bins, uint32_t rem, uint32_t *wsum, uint3 *found) {
   static_assert(PER % 4 == 0, "whole 16-byte groups");
   const int top = 64 * W * PER - PER * ((int)threadIdx.x + 1);  // this thread's bins: top + PER - 1 down to top
   uint32_t x[PER], sum = 0;
@@ -132,7 +132,7 @@ __device__ __forceinline__ uint32_t find_bin(const uint32_t *bins, uint32_t rem,
   if (cum < rem && cum + sum >= rem) {
 #pragma unroll
     for (int i = PER - 1; i >= 0; --i) {
-      if (cum < rem && cum + x[i] >= rem) *found = make_uint2((uint32_t)(top + i), cum);
+      if (cum < rem && cum + x[i] >= rem) *found = make_uint3((uint32_t)(top + i), cum, x[i]);
       cum += x[i];
     }
   }

@@ -1538,7 +1538,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_keep_list(const int32_t *__re
                                                              int ncand, int64_t cap, SmallSel S) {
   constexpr int W = SPLIT_THREADS / 64;
   __shared__ uint32_t wsum[2][W];
-  __shared__ uint2 s_bin;
+  __shared__ uint3 s_bin;
   __shared__ uint32_t s_at;
   __shared__ uint32_t h[SEL_BINS];
   const int64_t q = blockIdx.x / P;
@@ -1550,7 +1550,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_keep_list(const int32_t *__re
   const bool all = nhit <= (uint32_t)ncand;  // no more hits than candidates: all are listed
   const uint32_t b1 = all ? 0 : s_bin.x;
   // the whole list's length
-  const uint32_t nl = all ? nhit : s_bin.y + hist1[q * SEL_BINS + b1];
+  const uint32_t nl = all ? nhit : s_bin.y + s_bin.z;
   uint32_t n = 0;
 #pragma unroll
   for (int i = 0; i < 16; ++i) n += x[i] != NO_HIT && (fp_key(x[i]) >> 20) >= b1;
@@ -1610,7 +1610,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_keep_cut(const int32_t *__restr
   constexpr int W = SEL_THREADS / 64, PER = SEL_BINS / SEL_THREADS;
   __shared__ __align__(16) uint32_t hist[2][SEL_BINS];
   __shared__ uint32_t wsum[5][W];
-  __shared__ uint2 s_bin[3];
+  __shared__ uint3 s_bin[3];
   __shared__ uint32_t s_cnt[CUT_CHUNKS][2], s_done;
   extern __shared__ uint32_t chunk_n[];  // [P] kept, [P] tied
   const bool one = (int64_t)blockIdx.x < nq;  // the whole list by this workgroup

@@ -358,14 +358,18 @@ void launch_residual_score(const uint16_t *Qs, int64_t nq, int Tq, int TQP, cons
 // (F^ desc, doc asc) among the kept candidates, then a bitonic sort of the
 // k winners in LDS.  The keys' common high bits are skipped (the scores of a
 // query's candidates share most of them) and each pass takes 12 bits, so one
-// or two passes decide; up to TOPK_REGS keys of a thread stay in registers.
+// or two passes decide; up to REGS keys of a thread stay in registers.
 // One query with 16,384 candidates and k = 100: 28.4 us with 8-bit passes from
-// the top over memory, now 18.3 us.
+// the top over memory, now 18.3 us.  With room for 16 keys a thread (75 VGPRs)
+// a CU holds one workgroup, with room for 1 or 4 two, so the registers go by
+// ncand: 300 queries of 64 candidates 12 us (20 with 16 keys a thread, 10 with
+// 8-bit passes), 1024 of 4096 27 us (47 and 44), one of 64 9 us (11 and 8).
 constexpr int TOPK_THREADS = 1024;
 constexpr int TOPK_REGS = 16;
 constexpr int TOPK_BINS = 4096;
 
-__global__ __launch_bounds__(TOPK_THREADS) void k_topk(const int32_t *__restrict__ fhat,
+template <int REGS>
+__global__ __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_eu(REGS == TOPK_REGS ? 4 : 8))) void k_topk(const int32_t *__restrict__ fhat,
                                                        const int32_t *__restrict__ cand_ids,
                                                        const int32_t *__restrict__ n_valid, int ncand, int k, int kpow2,
                                                        int32_t *__restrict__ ids, float *__restrict__ scores) {
@@ -373,7 +377,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void k_topk(const int32_t *__restrict
   extern __shared__ uint64_t sk[];  // [kpow2]
   __shared__ __align__(16) uint32_t hist[TOPK_BINS];
   __shared__ uint32_t wsum[W];
-  __shared__ uint2 s_bin;
+  __shared__ uint3 s_bin;
   __shared__ unsigned long long s_and[W], s_or[W];
   __shared__ int s_count;
   const int64_t q = blockIdx.x;
@@ -381,11 +385,11 @@ __global__ __launch_bounds__(TOPK_THREADS) void k_topk(const int32_t *__restrict
   const int m = min(k, n);
   const int32_t *fh = fhat + q * ncand;
   const int32_t *ci = cand_ids + q * ncand;
-  const bool in_regs = n <= TOPK_REGS * TOPK_THREADS;  // uniform
-  unsigned long long r[TOPK_REGS];  // 0: no key (a real key is larger)
+  const bool in_regs = REGS < TOPK_REGS || n <= REGS * TOPK_THREADS;  // uniform
+  unsigned long long r[REGS];  // 0: no key (a real key is larger)
   if (in_regs) {
 #pragma unroll
-    for (int u = 0; u < TOPK_REGS; ++u) {
+    for (int u = 0; u < REGS; ++u) {
       const int i = threadIdx.x + u * TOPK_THREADS;
       r[u] = i < n ? pack_key(fh[i], (uint32_t)ci[i]) : 0;
     }
@@ -393,7 +397,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void k_topk(const int32_t *__restrict
   auto each = [&](auto &&g) {
     if (in_regs) {
 #pragma unroll
-      for (int u = 0; u < TOPK_REGS; ++u)
+      for (int u = 0; u < REGS; ++u)
         if (r[u]) g(r[u]);
     } else {
       for (int i = threadIdx.x; i < n; i += TOPK_THREADS) g(pack_key(fh[i], (uint32_t)ci[i]));
@@ -436,7 +440,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void k_topk(const int32_t *__restrict
       });
       __syncthreads();
       find_bin<W, TOPK_BINS / TOPK_THREADS>(hist, rem, wsum, &s_bin);
-      const uint32_t bin = s_bin.x, here = hist[bin];
+      const uint32_t bin = s_bin.x, here = s_bin.z;
       rem -= s_bin.y;
       T |= (unsigned long long)bin << shift;
       // the whole bin is needed: every key >= its base is taken (with every
@@ -482,19 +486,28 @@ __global__ __launch_bounds__(TOPK_THREADS) void k_topk(const int32_t *__restrict
   }
 }
 
-void launch_topk(const int32_t *fhat, const int32_t *cand_ids, const int32_t *n_valid, int64_t nq, int ncand, int k,
-                 int32_t *ids, float *scores, hipStream_t s) {
+template <int REGS>
+static void launch_topk_t(const int32_t *fhat, const int32_t *cand_ids, const int32_t *n_valid, int64_t nq, int ncand,
+                          int k, int32_t *ids, float *scores, hipStream_t s) {
   int kp = 1;
   while (kp < k) kp <<= 1;
   // k up to 8192: 64 KiB of dynamic LDS beside the static state, above the
   // default per-workgroup limit
   static bool attr = [] {
-    return hipFuncSetAttribute((const void *)k_topk, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024) ==
+    return hipFuncSetAttribute((const void *)k_topk<REGS>, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024) ==
            hipSuccess;
   }();
   (void)attr;
-  hipLaunchKernelGGL(k_topk, dim3((unsigned)nq), dim3(TOPK_THREADS), (size_t)kp * 8, s, fhat, cand_ids, n_valid, ncand,
-                     k, kp, ids, scores);
+  hipLaunchKernelGGL(k_topk<REGS>, dim3((unsigned)nq), dim3(TOPK_THREADS), (size_t)kp * 8, s, fhat, cand_ids, n_valid,
+                     ncand, k, kp, ids, scores);
+}
+
+void launch_topk(const int32_t *fhat, const int32_t *cand_ids, const int32_t *n_valid, int64_t nq, int ncand, int k,
+                 int32_t *ids, float *scores, hipStream_t s) {
+  auto *launch = ncand <= TOPK_THREADS       ? launch_topk_t<1>
+                 : ncand <= 4 * TOPK_THREADS ? launch_topk_t<4>
+                                             : launch_topk_t<TOPK_REGS>;
+  launch(fhat, cand_ids, n_valid, nq, ncand, k, ids, scores, s);
 }
 
 }  // namespace chimera

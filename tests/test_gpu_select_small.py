@@ -89,3 +89,30 @@ def test_a_long_list_is_not_cut_by_one_workgroup(monkeypatch):
     say("select of one query, us:", best)
     assert max(best.values()) < 300, best
     idx.close()
+
+
+@pytest.mark.parametrize("ncand", [1024, 1025, 4096, 4097])
+def test_topk_at_the_edges_of_its_registers(ncand):
+    """1, 4 and 16 keys a thread; k of 1, some and every candidate; a tied query."""
+    w, c, _, _, oi, idx = setup("tiny", ndocs=12_289, ncent=256, len_kind=2, len_lo=1, len_hi=4)
+    q, _ = c.queries(3, 32, query_seed=ncand)
+    q[1] = 0
+    for k in (1, 37, ncand):
+        check_search(idx, oi, q, 32, ncand, k, "bf16", f"top-k, ncand {ncand}, k {k}")
+
+
+def test_topk_of_few_candidates_keeps_two_workgroups_a_cu(monkeypatch):
+    """512 queries of 64 candidates take little longer in the top-k than 256
+    (1.3 times; 1.6 when a CU holds one workgroup)."""
+    monkeypatch.setenv("CHIMERA_STAGE_TIMING", "1")
+    w, c, _, _, _, _ = setup("tiny", ndocs=12_289, ncent=256, len_kind=2, len_lo=1, len_hi=4)
+    idx = product_builder(c, w.nbits).upload(0)
+    Q = q_tensor(c.queries(512, 8, query_seed=1)[0], "bf16")
+    best = {}
+    for _ in range(40):
+        for nq in (256, 512):
+            idx.search(Q[:nq], 4, 64, 10)
+            best[nq] = min(best.get(nq, 1e9), 1e3 * float(idx.stage_times()[5]))
+    say("top-k, us:", best)
+    assert best[512] < 1.45 * best[256], best
+    idx.close()
