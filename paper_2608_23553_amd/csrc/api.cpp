@@ -457,7 +457,7 @@ static int run(chimera_index *idx, const void *Q, int q_dtype, int64_t nq, int T
                          idx->d_doc_off, idx->d_codes, idx->nbits, idx->h_weights, idx->ndocs,
                          idx->ndeleted ? idx->d_deleted : nullptr, fp, hist, s);
     else
-      launch_cand_walk(ci, ck, nb, Tq, TQP, nprobe, idx->d_ivf_off, idx->d_ivf_doc, idx->ndocs, idx->ncent,
+      launch_cand_walk(ci, ck, nb, Tq, TQP, nprobe, idx->d_ivf_off, idx->d_ivf_doc, idx->ndocs, idx->nnz, idx->ncent,
                        idx->ndense, idx->d_dense_slot, idx->d_doc_dense, idx->ndeleted ? idx->d_deleted : nullptr, fp,
                        hist, s);
     CHIMERA_HIP(hipGetLastError());

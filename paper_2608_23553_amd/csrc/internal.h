@@ -130,9 +130,9 @@ void launch_list_walk(const int32_t *cent_ids, const int32_t *cent_keys, int64_t
                       const uint64_t *deleted, int32_t *fp, uint32_t *hist, hipStream_t s);
 // Whether launch_cand_walk goes through chains and a table (k_prune.hip) with
 // workgroups of M ranges.
-bool walk_by_chains(int Tq, int TQP, int nprobe, int ncent, int ndense, int M);
+bool walk_by_chains(int Tq, int TQP, int nprobe, int64_t ndocs, int64_t nnz, int ncent, int ndense, int M);
 void launch_cand_walk(const int32_t *cent_ids, const int32_t *cent_keys, int64_t nq, int Tq, int TQP, int nprobe,
-                      const int64_t *ivf_off, const int32_t *ivf_doc, int64_t ndocs, int ncent, int ndense,
+                      const int64_t *ivf_off, const int32_t *ivf_doc, int64_t ndocs, int64_t nnz, int ncent, int ndense,
                       const int8_t *dense_slot, const uint64_t *doc_dense, const uint64_t *deleted, int32_t *fp,
                       uint32_t *hist, hipStream_t s);
 

@@ -839,20 +839,24 @@ size_t walk_lds_bytes(int TQP, int nprobe, int Tq) {
                   list_walk_lds_bytes(TQP, nprobe, Tq));
 }
 
-// Whether the walk through chains and a table pays, for workgroups of M
-// ranges.  It saves a barrier and more per rank and range, but its table is
+// Whether the walk through chains and a table pays, for workgroups of M ranges
+// and lists of nnz entries in all.  It saves a barrier and more per rank and range, but its table is
 // built once per workgroup, and costs more the more dense groups a query has:
 // at 1M documents and one range a workgroup (128 queries) it takes 0.86, 0.97
 // and 1.11 of the time rank by rank at 8 ranks with 4, 16 and 32 query tokens,
 // 0.74, 0.84 and 0.93 at 16; with eight ranges (1024 queries) 0.71, 0.76 and
 // 0.99 at 8 ranks, 0.80, 0.87 and 1.03 at 4.  Queries of more than
-// WALK_TAB_BITS dense groups gain nothing: with 64 tokens most have them
-// (1.00 to 1.07 at every rank count), and with few centroids the lower ranks
-// add groups to the tokens' own, about (nprobe - 1) Tq ndense / ncent (100,000
+// WALK_TAB_BITS dense groups gain nothing: with 64 tokens most have them (1.00
+// to 1.07 at every rank count on 1M and 2.2M documents), and with few centroids
+// the lower ranks add groups to the tokens' own, about (nprobe - 1) Tq ndense /
+// ncent.  Nor do ranges with more entries than the chains hold; the lower ranks'
+// lists bring about 4096 (nprobe - 1) Tq nnz / (ndocs ncent).  (100,000
 // documents, 16,384 centroids, 32 tokens: 1.01 at 16 ranks, 1.05 at 32; 1M,
-// 65,536 centroids, 64 ranks: 1.13, where 32 ranks take 0.82).
-bool walk_by_chains(int Tq, int TQP, int nprobe, int ncent, int ndense, int M) {
-  if (TQP != 32 || (int64_t)(nprobe - 1) * Tq * ndense > ncent) return false;
+// 65,536 centroids, 64 ranks: 1.13, where 32 ranks take 0.82; 313,900 and 15,644,
+// 26 tokens, 22 ranks: 1.17; but 4,676 and 4,904, 13 tokens, 12 ranks: 0.44.)
+bool walk_by_chains(int Tq, int TQP, int nprobe, int64_t ndocs, int64_t nnz, int ncent, int ndense, int M) {
+  const double lower = (double)(nprobe - 1) * Tq / ncent;
+  if (TQP != 32 || lower * ndense > 2 || 4096 * lower * (double)nnz > (double)WALK_NODES * (double)ndocs) return false;
   if (Tq > 16) return nprobe >= 16 || (nprobe >= 8 && M >= 3);
   return M * nprobe >= (Tq > 8 ? 12 : 8);
 }
@@ -889,7 +893,7 @@ static void launch_walk_r(const int32_t *cent_ids, const int32_t *cent_keys, int
 }
 
 void launch_cand_walk(const int32_t *cent_ids, const int32_t *cent_keys, int64_t nq, int Tq, int TQP, int nprobe,
-                      const int64_t *ivf_off, const int32_t *ivf_doc, int64_t ndocs, int ncent, int ndense,
+                      const int64_t *ivf_off, const int32_t *ivf_doc, int64_t ndocs, int64_t nnz, int ncent, int ndense,
                       const int8_t *dense_slot, const uint64_t *doc_dense, const uint64_t *deleted, int32_t *fp, uint32_t *hist,
                       hipStream_t s) {
   if (nq <= 0) return;
@@ -910,8 +914,9 @@ void launch_cand_walk(const int32_t *cent_ids, const int32_t *cent_keys, int64_t
   const int M = (nranges + G - 1) / std::max(1, G);
   G = (nranges + M - 1) / std::max(1, M);
   auto *launch = TQP != 32 ? launch_walk_r<unsigned long long, 2048, false>
-                 : walk_by_chains(Tq, TQP, nprobe, ncent, ndense, M) ? launch_walk_r<uint32_t, 4096, true>
-                                                                     : launch_walk_r<uint32_t, 4096, false>;
+                 : walk_by_chains(Tq, TQP, nprobe, ndocs, nnz, ncent, ndense, M)
+                     ? launch_walk_r<uint32_t, 4096, true>
+                     : launch_walk_r<uint32_t, 4096, false>;
   launch(cent_ids, cent_keys, nq, Tq, TQP, nprobe, ivf_off, ivf_doc, ndocs, ncent, ndense, dense_slot, doc_dense,
          deleted, nranges, G, M, fp, hist, s);
 }

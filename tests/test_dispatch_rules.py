@@ -34,21 +34,30 @@ def test_select_scratch_does_not_depend_on_the_select(nq):
             assert f(nq, ndocs, ncand) == _split_select_bytes(nq, ndocs, ncand), (nq, ndocs, ncand)
 
 
-@pytest.mark.parametrize("chains,Tq,nprobe,ncent,M", [
+# the corpora that both walks were timed on: documents, centroids, distinct centroids of a document's tokens
+Z100 = (100_000, 16_384, 45)
+Z1M = (1_000_000, 65_536, 49)
+Z22 = (2_200_000, 262_144, 53)
+
+
+@pytest.mark.parametrize("chains,Tq,nprobe,on,M", [
     # measured faster through chains and the table (time against rank by rank)
-    (True, 4, 8, 65_536, 1), (True, 16, 16, 65_536, 1), (True, 32, 16, 65_536, 1),    # 0.86, 0.84, 0.93
-    (True, 32, 32, 65_536, 8), (True, 16, 4, 65_536, 8), (True, 32, 8, 262_144, 9),   # 0.80, 0.87, 0.94
-    (True, 8, 32, 16_384, 1), (True, 16, 64, 65_536, 1),                              # 0.47, 0.44
+    (True, 4, 8, Z1M, 1), (True, 16, 16, Z1M, 1), (True, 32, 16, Z1M, 1),    # 0.86, 0.84, 0.93
+    (True, 32, 32, Z1M, 8), (True, 16, 4, Z1M, 8), (True, 32, 8, Z22, 9),    # 0.80, 0.87, 0.94
+    (True, 8, 32, Z100, 1), (True, 16, 64, Z1M, 1), (True, 32, 64, Z22, 3),  # 0.47, 0.44, 0.67
+    (True, 13, 12, (4676, 4904, 31), 1),                                     # 0.44
     # measured slower
-    (False, 32, 8, 65_536, 1), (False, 32, 4, 262_144, 1), (False, 32, 4, 65_536, 8),  # 1.11 to 1.22, 1.34, 1.03
-    (False, 16, 4, 65_536, 1), (False, 4, 1, 65_536, 1), (False, 8, 1, 16_384, 1),     # 1.07 to 1.11, 1.09, 1.10
-    (False, 32, 64, 65_536, 1), (False, 32, 32, 16_384, 1),                            # 1.13, 1.05
-    (False, 64, 8, 65_536, 1), (False, 64, 32, 65_536, 1), (False, 64, 16, 262_144, 5),  # 1.02, 1.04, 1.03
+    (False, 32, 8, Z1M, 1), (False, 32, 4, Z22, 1), (False, 32, 4, Z1M, 8),  # 1.11 to 1.22, 1.34, 1.03
+    (False, 16, 4, Z1M, 1), (False, 4, 1, Z1M, 1), (False, 8, 1, Z100, 1),   # 1.07 to 1.11, 1.09, 1.10
+    (False, 32, 64, Z1M, 1), (False, 32, 32, Z100, 1),                       # 1.13, 1.05
+    (False, 26, 22, (313_900, 15_644, 37), 1),                               # 1.17
+    (False, 64, 8, Z1M, 1), (False, 64, 32, Z1M, 1), (False, 64, 16, Z22, 5),  # 1.02, 1.04, 1.03
 ])
-def test_walk_through_chains_where_it_was_measured_faster(chains, Tq, nprobe, ncent, M):
+def test_walk_through_chains_where_it_was_measured_faster(chains, Tq, nprobe, on, M):
     """Indexes of 64 dense lists, workgroups of M ranges."""
-    f = _fn("_ZN7chimera14walk_by_chainsEiiiiii", ctypes.c_bool, *[ctypes.c_int] * 6)
-    assert f(Tq, 32 if Tq <= 32 else 64, nprobe, ncent, 64, M) == chains
+    ndocs, ncent, distinct = on
+    f = _fn("_ZN7chimera14walk_by_chainsEiiilliii", ctypes.c_bool, I32, I32, I32, I64, I64, I32, I32, I32)
+    assert f(Tq, 32 if Tq <= 32 else 64, nprobe, ndocs, ndocs * distinct, ncent, 64, M) == chains
 
 
 _GROUPED = "_ZN7chimera17doc_score_groupedEliiillliiiib"

@@ -109,10 +109,12 @@ def test_chains_overflow_in_a_workgroups_second_range(row, nprobe):
         assert bool((cand[:, i] == cand[0, i]).all()) and bool((keys[:, i] == keys[0, i]).all()), i
 
 
-def _by_chains(Tq, nprobe, ncent, ndense, M):
-    f = chimera.lib()._ZN7chimera14walk_by_chainsEiiiiii
-    f.restype = ctypes.c_bool
-    return f(Tq, 32 if Tq <= 32 else 64, nprobe, ncent, ndense, M)
+def _by_chains(idx, Tq, nprobe, ndense, M):
+    f = chimera.lib()._ZN7chimera14walk_by_chainsEiiilliii
+    i32, i64 = ctypes.c_int32, ctypes.c_int64
+    f.restype, f.argtypes = ctypes.c_bool, [i32, i32, i32, i64, i64, i32, i32, i32]
+    i = idx.info()
+    return f(Tq, 32 if Tq <= 32 else 64, nprobe, i["ndocs"], i["nnz"], i["ncent"], ndense, M)
 
 
 def _dense(c, cl, ndocs, ncent, R=4096):
@@ -128,14 +130,14 @@ def _dense(c, cl, ndocs, ncent, R=4096):
     (9001, 65_536, 16, 32, None),        # 10 to 15 dense groups: both ways in one batch; a ragged last range
     (9001, 65_536, 32, 32, None),        # two lists a thread
     (4096, 16_384, 16, 16, None),        # one whole range
-    (9001, 8192, 16, 8, (100, 180)),     # some ranges hold more entries than the chains
-    (16_384, 16_384, 16, 16, (60, 160)),
+    (9001, 8192, 16, 8, (50, 150)),      # long chains
+    (16_384, 16_384, 16, 16, (50, 150)),  # some ranges hold more entries than the chains
     (5000, 4096, 9, 7, None),            # few tokens
 ])
 def test_prune_by_chains(ndocs, ncent, nprobe, Tq, lens):
     kw = dict(len_kind=2, len_lo=lens[0], len_hi=lens[1]) if lens else {}
     w, c, _, cl, oi, idx = setup("1m", ndocs=ndocs, ncent=ncent, **kw)
-    assert _by_chains(Tq, nprobe, ncent, len(_dense(c, cl, ndocs, ncent)[1]), 1)
+    assert _by_chains(idx, Tq, nprobe, len(_dense(c, cl, ndocs, ncent)[1]), 1)
     q, _ = c.queries(24, Tq, query_seed=5)
     q[4] = np.repeat(q[4, :(Tq + 3) // 4], 4, axis=0)[:Tq]  # tokens four times over
     _check_prune(idx, oi.prune(q, nprobe, ndocs), q, nprobe, ndocs, f"chains: {ndocs} {ncent} {nprobe} {Tq} {lens}")
@@ -147,7 +149,7 @@ def test_second_range_past_the_chains_by_chains():
     ndocs = ncent = 16_384
     w, c, _, cl, oi, idx = setup("1m", ndocs=ndocs, ncent=ncent, len_kind=2, len_lo=50, len_hi=150)
     count, dense = _dense(c, cl, ndocs, ncent)
-    assert _by_chains(16, 16, ncent, len(dense), 2)
+    assert _by_chains(idx, 16, 16, len(dense), 2)
     few = c.queries(400, 16, query_seed=5)[0][[14, 0, 1, 2, 3]]
     ids = np.asarray(oracle.probe(oracle.centroid_scores(few[0], c.centroids_k), 16)[0])
     entries = sum(count[np.setdiff1d(ids[:, r], dense)].sum(0) for r in range(16))
@@ -169,6 +171,6 @@ def test_second_range_past_the_chains_by_chains():
 def test_prune_rank_by_rank(nprobe, Tq):
     """Either mask width with one, two and four lists a thread."""
     w, c, _, cl, oi, idx = setup("1m", ndocs=9001, ncent=8192)
-    assert not _by_chains(Tq, nprobe, 8192, len(_dense(c, cl, 9001, 8192)[1]), 1)
+    assert not _by_chains(idx, Tq, nprobe, len(_dense(c, cl, 9001, 8192)[1]), 1)
     q, _ = c.queries(9, Tq, query_seed=nprobe)
     _check_prune(idx, oi.prune(q, nprobe, 9001), q, nprobe, 9001, f"ranks: {nprobe} {Tq}")
