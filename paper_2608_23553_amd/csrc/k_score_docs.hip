@@ -743,17 +743,25 @@ static Visits sort_visits(int64_t nq, int64_t ndocs, const int32_t *cand_ids, co
 // 1024 queries of 4 to 64 tokens and 0.5 to 42 visits a document.  Within about
 // a tenth they take, in ns,
 //   by query     30e3 + 0.044 nq ncent B + b V L
-//   by document  78e3 + 0.022 nq ncent B + d D L + 0.0108 B V L + 0.83 ndocs
+//   by document  78e3 + 0.022 nq ncent B + d D L + 0.0108 B V L + 0.83 ndocs + P
 // for V visits, D documents with a visit, L tokens a document and B blocks of
 // 32 query tokens.  b is 0.013 at 4 and 0.019 at 32 query tokens (a row of S^T
-// that several tokens share is read once), 0.034 at 64, and 0.025 a block with
-// 4-bit codes; d, the decoding, 0.020 and 0.033.  So few query tokens and few
+// that several tokens share is read once), 0.034 at 64; with 4-bit codes a tenth
+// more, and 0.025 a block where a query's S^T is past an L2; d, the decoding,
+// 0.020 and 0.033.  So few query tokens and few
 // visits a document go by query: by document takes 1.5 times as long with 64
 // queries of 4 tokens and 4096 candidates on 100,000 documents, 1.3 times with
 // 256 and 8192 on 1M, where 32 tokens take 0.96 and 1024 queries 0.73.
 //
 // A visit here is a kept candidate: no more than the probed lists hold, where
 // the lists are about even.
+//
+// With dense lists some documents are kept by many queries, in small
+// collections by nearly all (p, taken as 16 ncand / ndocs), and the workgroups
+// that score them are busy for 8 B p nq L together: P is what that is above half
+// of the other workgroups' time (the terms of D, V and ndocs).  938 queries of 51
+// tokens on 2,211 documents, 4-bit codes: probe and scoring 0.98 ms by document
+// and 0.56 by query with 87 candidates, 1.64 and 1.25 with 400.
 //
 // One workgroup scores a document, so a document far longer than the others
 // keeps the rest of the chip waiting: with 256 queries of 4096 candidates on
@@ -783,13 +791,16 @@ bool doc_score_grouped(int64_t nq, int Tq, int nprobe, int ncand, int64_t ndocs,
   double kept = ncand;
   if (ndense == 0) kept = std::min(kept, (double)Tq * nprobe * (double)nnz / ncent);
   if (max_doc_len > 4 * L && max_doc_len > (rq ? 0.7 : 0.4) * kept * L / 256) return false;
-  if (rq) return Tq > 32 || ncand >= 1024;
+  if (rq) return ncand >= 1024 || (Tq > 32 && ndense == 0);
   const double B = Tq > 32 ? 2 : 1, V = (double)nq * kept;
   const double D = n * (1 - std::exp(-(ndense > 0 ? 0.5 : 1.0) * V / n));
-  const double b = nbits == 4 ? 0.025 + 0.022 * (B - 1) : 0.0127 + 0.0093 * (B - 1) + 0.000185 * Tq;
+  const double b2 = 0.0127 + 0.0093 * (B - 1) + 0.000185 * Tq;
+  const double b = nbits != 4 ? b2 : (double)ncent * B < 32768 ? 1.1 * b2 : 0.025 + 0.022 * (B - 1);
   const double by_query = 30e3 + 0.044 * (double)nq * ncent * B + b * V * L;
-  const double by_doc = 78e3 + 0.022 * (double)nq * ncent * B + (nbits == 4 ? 0.033 : 0.020) * D * L +
-                        0.0108 * B * V * L + 0.83 * n;
+  const double spread = (nbits == 4 ? 0.033 : 0.020) * D * L + 0.0108 * B * V * L + 0.83 * n;
+  const double p = std::min(1.0, 16.0 * ncand / n);
+  const double popular = ndense > 0 ? std::max(0.0, 8 * B * p * (double)nq * L - 0.5 * spread) : 0.0;
+  const double by_doc = 78e3 + 0.022 * (double)nq * ncent * B + spread + popular;
   // (20 us in its favour: in small batches it was measured closer than that)
   return by_doc - 20e3 < by_query;
 }

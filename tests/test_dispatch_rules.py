@@ -91,6 +91,10 @@ LONG = dict(ndocs=250_000, L=320, ncent=65_536, longest=512, nbits=4)
     (False, 256, 4, 4, 2048, ZIPF),                                                                  # 1.11
     (False, 256, 4, 4, 8192, M1), (False, 256, 16, 4, 8192, M1), (False, 512, 4, 4, 4096, M1),       # 1.38 1.11 1.23
     (False, 256, 8, 8, 16_384, SHARD), (False, 4, 64, 8, 32_768, LONG),                              # 1.15 1.24
+    (False, 938, 51, 5, 87, dict(ndocs=2211, L=77, ncent=2685, ndense=64, nbits=4)),                 # 1.73
+    (False, 938, 51, 5, 400, dict(ndocs=2211, L=77, ncent=2685, ndense=64, nbits=4)),                # 1.31
+    (False, 300, 51, 5, 400, dict(ndocs=2211, L=77, ncent=2685, ndense=64, nbits=4)),                # 1.27
+    (False, 762, 32, 20, 278, dict(ndocs=4309, L=77, ncent=1714, ndense=64)),                        # 1.06
     # one document keeps the chip waiting
     (False, 256, 32, 4, 4096, dict(EVEN, longest=1200)), (False, 1024, 32, 4, 4096, dict(EVEN, longest=40_000)),
     (False, 256, 32, 8, 8192, dict(M1, longest=2000)), (False, 256, 32, 4, 4096, dict(EVEN, L=74.7, longest=600)),
