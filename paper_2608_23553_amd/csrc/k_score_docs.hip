@@ -30,12 +30,13 @@
 // 32x32x16 (256 cycles of a SIMD) per 32 document tokens and 32 query tokens.
 // A wave keeps 64 query columns in registers, so each 8 KB tile read from LDS
 // feeds 16 MFMA (64 bytes per clock and CU, half of what LDS delivers).
-// Measured with 1024 queries of 16,384 candidates on 2.2M documents: 20.4 ms
-// against 29.1 ms by query, 1.03 PFLOP/s at 1.69 GHz, the matrix cores 58%
-// busy; 128 queries of 64 tokens and 32,768 candidates on 250,000 documents of
-// 320 tokens (4-bit codes): 26.8 ms against 67.0 ms, 1.16 PFLOP/s, 64% busy (a
-// loop of nothing but these MFMA reaches 1.6 to 1.76 PFLOP/s here).  The
-// probe, which no longer writes S^T, falls from 10.0 to 7.6 ms in the first.
+// Measured with 1024 queries of 16,384 candidates on 2.2M documents: 20.5 ms
+// against 29.1 ms by query, 1.05 PFLOP/s, the matrix cores 61% busy; 128
+// queries of 64 tokens and 32,768 candidates on 250,000 documents of 320
+// tokens (4-bit codes): 26.8 ms against 67.0 ms, 1.16 PFLOP/s (a loop of
+// nothing but these MFMA reaches 1.6 to 1.76 PFLOP/s here).  The probe, which
+// no longer writes S^T, falls from 10.0 to 7.6 ms in the first (4.0 ms since,
+// the centroids in operand order).
 // Also tried, all slower for short documents: one query's columns per wave
 // with eight waves a workgroup (LDS reads double), 16 lanes to a token in the
 // decoder (fewer cache lines per load, a longer chain), documents decoded into
